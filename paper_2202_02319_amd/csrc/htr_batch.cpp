@@ -26,6 +26,7 @@ Ctx htr::bview(const htr_batch* b) {
   v.ndtblocks = b->ndtblocks;
   v.grid = b->grid;
   v.conv_split = b->conv_split;
+  v.om_tab = b->ctx->om_tab;
   v.scheme = b->ctx->scheme;
   v.total_cells = b->Ntot;
   v.timer = const_cast<Timer*>(&b->timer);

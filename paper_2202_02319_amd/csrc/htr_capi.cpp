@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -65,6 +66,81 @@ htr_status check_laser(const htr_laser* L) {
   return HTR_OK;
 }
 
+// Tabulates Omega11 (the Neufeld-Janzen-Aziz fit) over the mechanism's range
+// of T* = T / (eps_ij / k): on each interval the Chebyshev interpolant of
+// degree OMDEG, formed in extended precision and stored as coefficients of
+// T* - centre.  The interval's half width is a 1/65 of T* at most, so the
+// fastest exponential, exp(-3.89411 T*), leaves a remainder below
+// 1.8 (a/64)^8 exp(-a) / (2^7 8!) with a = 3.89 T*, 7e-18 where it is largest.
+static void tabulate_omega11(MechTables* T) {
+  double lo = INFINITY, hi = 0.0;
+  for (int i = 0; i < T->ns; ++i)
+    for (int j = 0; j < T->ns; ++j) {
+      lo = std::fmin(lo, T->Tmin * T->Dieps[i][j]);
+      hi = std::fmax(hi, T->Tmax * T->Dieps[i][j]);
+    }
+  T->omrow0 = T->omrows = 0;
+  if (!(lo > 1e-300) || !(hi < 1e5)) return;
+  auto row_of = [](double x) {
+    uint64_t b;
+    std::memcpy(&b, &x, 8);
+    return (int)(b >> 47);
+  };
+  const int r0 = row_of(lo), n = row_of(hi) - r0 + 1;
+  if (n > OMROWS) return;
+  // x = 2^e m (1 + d cos): the power is a product over octave and mantissa,
+  // each exponential one over the interval's centre and the node's offset,
+  // so a row costs three exponentials
+  constexpr int K = OMDEG + 1;
+  const long double pi = 3.14159265358979323846264338327950288L;
+  const long double rate[3] = {0.47635L, 1.52996L, 3.89411L}, amp[3] = {0.19300L, 1.03587L, 1.76474L};
+  long double cs[4 * K], pm[OMSUB][K], off[3][K];
+  for (int k = 0; k < 4 * K; ++k) cs[k] = cosl(pi * k / (2 * K));
+  for (int i = 0; i < OMSUB; ++i)
+    for (int k = 0; k < K; ++k)
+      pm[i][k] = powl(1.0L + (2 * i + 1 + cs[2 * k + 1]) / (2.0L * OMSUB), -0.15610L);
+  int oct = INT_MIN;
+  long double pe = 0.0L;
+  for (int r = 0; r < n; ++r) {
+    const uint64_t b0 = (uint64_t)(r0 + r) << 47, bc = b0 | (1ull << 46);
+    double x0, xc;
+    std::memcpy(&x0, &b0, 8);
+    std::memcpy(&xc, &bc, 8);
+    const long double h = (long double)xc - (long double)x0;
+    const int e = std::ilogb(x0), i = (r0 + r) & (OMSUB - 1);
+    if (e != oct) {
+      oct = e;
+      pe = 1.06036L * powl(2.0L, -0.15610L * e);
+      for (int a = 0; a < 3; ++a)
+        for (int k = 0; k < K; ++k) off[a][k] = amp[a] * expl(-rate[a] * h * cs[2 * k + 1]);
+    }
+    const long double ec[3] = {expl(-rate[0] * xc), expl(-rate[1] * xc), expl(-rate[2] * xc)};
+    long double f[K], ch[K], mono[K] = {}, t0[K] = {1.0L}, t1[K] = {0.0L, 1.0L};
+    for (int k = 0; k < K; ++k) f[k] = pe * pm[i][k] + ec[0] * off[0][k] + ec[1] * off[1][k] + ec[2] * off[2][k];
+    for (int j = 0; j < K; ++j) {
+      ch[j] = 0.0L;
+      for (int k = 0; k < K; ++k) ch[j] += f[k] * cs[j * (2 * k + 1) % (4 * K)];
+      ch[j] *= (j == 0 ? 1.0L : 2.0L) / K;
+    }
+    for (int j = 0; j < K; ++j) {   // the polynomials T_j in powers of (x - xc) / h
+      for (int k = 0; k < K; ++k) mono[k] += ch[j] * t0[k];
+      long double t2[K];
+      for (int k = 0; k < K; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
+      for (int k = 0; k < K; ++k) {
+        t0[k] = t1[k];
+        t1[k] = t2[k];
+      }
+    }
+    long double ih = 1.0L;
+    for (int k = 0; k < K; ++k) {
+      T->om11[r][k] = (double)(mono[k] * ih);
+      ih /= h;
+    }
+  }
+  T->omrow0 = r0;
+  T->omrows = n;
+}
+
 htr_status build_tables(const htr_mech_desc* m, MechTables* T) {
   if (!m) return fail(HTR_EINVAL, "mechanism descriptor is NULL");
   if (m->ns < 1) return fail(HTR_EINVAL, "ns must be >= 1 (got %d)", m->ns);
@@ -110,7 +186,14 @@ htr_status build_tables(const htr_mech_desc* m, MechTables* T) {
     T->lneps[s] = std::log(ek);
     T->pw22[s] = std::pow(ek, 0.14874);
     T->euck[s] = 1.25 * RU / W;
+    T->gc[s][0] = a[0] - a[6];
+    for (int k = 1; k < 5; ++k) T->gc[s][k] = -a[k] / (double)(k * (k + 1));
+    T->gc[s][5] = a[5];
+    T->imu_pre[s] = 1.0 / T->mu_pre[s];
+    T->rsW[s] = std::sqrt(W);
+    T->qW[s] = std::pow(W, -0.25);
   }
+  T->lnP0 = std::log(PREF / RU);
   for (int i = 0; i < ns; ++i)
     for (int j = 0; j < ns; ++j) {
       const double Wi = m->W[i], Wj = m->W[j];
@@ -153,7 +236,15 @@ htr_status build_tables(const htr_mech_desc* m, MechTables* T) {
     T->nre[j] = nre;
     T->npr[j] = npr;
     T->dnu[j] = (double)dnu;
+    int nf = 0, np = 0;
+    for (int e = 0; e < SIDE * 3; ++e) T->rfac[j][e] = T->pfac[j][e] = ns;
+    for (int e = 0; e < nre; ++e)
+      for (int k = 0; k < T->rnu[j][e]; ++k) T->rfac[j][nf++] = T->ridx[j][e];
+    for (int e = 0; e < npr; ++e)
+      for (int k = 0; k < T->pnu[j][e]; ++k) T->pfac[j][np++] = T->pidx[j][e];
+    T->nfac[j] = nf > np ? nf : np;
   }
+  if (ns > 1) tabulate_omega11(T);
   return HTR_OK;
 }
 
@@ -269,7 +360,7 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
   {
     TimedLaunch tl(C.timer, TC_POINT, s);
     HIP_OK(launch_point(C.ns, C.M, C.mem, C.nmem, C.nblocks, C.grid, a, U, T, w.aux, w.src, hrr,
-                        need_red ? w.blkred : nullptr, nullptr, w.status, want_dt, s, C.curv));
+                        need_red ? w.blkred : nullptr, nullptr, w.status, want_dt, C.om_tab, s, C.curv));
   }
   if (need_red) {
     TimedLaunch tl(C.timer, TC_REDUCE, s);
@@ -376,6 +467,7 @@ Ctx htr::view(const htr_ctx* c) {
   v.ndtblocks = c->ndtblocks;
   v.grid = c->grid;
   v.conv_split = c->conv_split;
+  v.om_tab = c->om_tab;
   v.scheme = c->scheme;
   v.total_cells = c->N;
   for (int a = 0; a < 3; ++a) {
@@ -432,6 +524,7 @@ htr_status htr_create(const htr_mech_desc* mech, const htr_grid_desc* grid, cons
   HIP_OK(hipGetDevice(&c->device));
   c->ns = T.ns;
   c->nr = T.nr;
+  c->om_tab = T.omrows > 0;
   c->scheme = *scheme;
   c->N = N;
   c->nblocks = (int)((N + BLK - 1) / BLK);
@@ -692,7 +785,7 @@ htr_status htr_cells(htr_ctx* c, const double* U, double* T_io, double t, const 
   a.flags = c->scheme.flags;
   hipStream_t s = (hipStream_t)stream;
   HIP_OK(launch_point(C.ns, C.M, C.mem, 1, C.nblocks, 0, a, U, T_io, c->ws.aux, c->ws.src, nullptr, nullptr, out,
-                      c->ws.status, 0, s, C.curv));
+                      c->ws.status, 0, C.om_tab, s, C.curv));
   if (C.curv)
     HIP_OK(launch_curv_sensor(C.mem, C.nblocks, *C.curv, c->ws.aux, C.ns, c->ws.flag, C.scheme.theta_c, out, s));
   else
@@ -709,7 +802,7 @@ htr_status htr_stable_dt(htr_ctx* c, const double* U, double* T_io, double* dt_d
   a.flags = c->scheme.flags | HTR_CHEM_OFF;   // the step limit needs no chemistry
   hipStream_t s = (hipStream_t)stream;
   HIP_OK(launch_point(C.ns, C.M, C.mem, 1, C.nblocks, 0, a, U, T_io, c->ws.aux, c->ws.src, nullptr, c->ws.blkred,
-                      nullptr, c->ws.status, 1, s, C.curv));
+                      nullptr, c->ws.status, 1, C.om_tab, s, C.curv));
   HIP_OK(launch_finalize(C.mem, 1, c->ws.blkred, c->scheme.cfl, dt_dev, nullptr, nullptr, 0.0, 1, s));
   return HTR_OK;
 }

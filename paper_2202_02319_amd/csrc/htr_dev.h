@@ -23,6 +23,11 @@ constexpr double PI = 3.14159265358979323846;
 // device status bits (first error wins by priority in htr_check)
 constexpr unsigned ST_NONFINITE = 1u, ST_NEWTON = 2u, ST_TRANGE = 4u;
 
+// Intervals of the tabulated collision integral: OMSUB per octave (the top
+// five mantissa bits of T*), so that degree 7 reaches the last bit; OMROWS
+// rows (20 KB of LDS) hold ten octaves of T*.
+constexpr int OMSUB = 32, OMDEG = 7, OMROWS = 320;
+
 // Mechanism tables, precomputed on the host in the forms the kernels use.
 struct MechTables {
   int ns, nr;
@@ -46,6 +51,19 @@ struct MechTables {
   int nre[MAXNR], npr[MAXNR];              // distinct reactant / product species
   int ridx[MAXNR][SIDE], rnu[MAXNR][SIDE];
   int pidx[MAXNR][SIDE], pnu[MAXNR][SIDE];
+  // the per-cell kernel's forms
+  double gc[MAXNS][6];                     // h/(RT) - s/R = gc[0] - cp[0] ln T + sum_{k=1..4} gc[k] T^k + gc[5]/T
+  double imu_pre[MAXNS];                   // 1 / mu_pre
+  double rsW[MAXNS], qW[MAXNS];            // sqrt(W), W^(-1/4)
+  double lnP0;                             // ln(p_ref / R_u)
+  int nfac[MAXNR];                         // factors of the longer side of a reaction's rates
+  int rfac[MAXNR][SIDE * 3];               // species of each factor of the forward rate (ns: the factor one)
+  int pfac[MAXNR][SIDE * 3];
+  // Omega11 as polynomials of degree OMDEG in T* on OMSUB intervals per
+  // octave, over [Tmin, Tmax] / (eps_ij / k); omrows = 0: the range needs
+  // more than OMROWS intervals and the kernel evaluates the fit itself
+  int omrow0, omrows;
+  double om11[OMROWS][OMDEG + 1];
 };
 
 struct LaserDev {
@@ -209,12 +227,13 @@ struct Workspace;
 hipError_t launch_prim_to_cons(int ns, const MechTables* M, const Member* mem, int nmem, int nblocks,
                                const double* Y, const double* T, const double* p, const double* vel, double* U,
                                hipStream_t s);
+// om_tab: the mechanism's collision integral is tabulated (MechTables::omrows > 0).
 // cg (nullable): the curvilinear geometry of a single-grid context (laser
 // over lattice images, contravariant dt limit, volume 1/J)
 hipError_t launch_point(int ns, const MechTables* M, const Member* mem, int nmem, int nblocks, int grid,
                         const CallArgs& a,
                         const double* U, double* T, double* aux, double* src, double* hrr, double* blkred,
-                        double* cells_out, unsigned* status, int want_dt, hipStream_t s,
+                        double* cells_out, unsigned* status, int want_dt, bool om_tab, hipStream_t s,
                         const CurvGeom* cg = nullptr);
 hipError_t launch_sensor(const Member* mem, int nmem, int nblocks, int grid, const double* aux, int ns,
                          unsigned char* flag,

@@ -89,6 +89,7 @@ struct Ctx {
   int ndtblocks = 0;              // diffusive-sweep launches
   int grid = 0;                   // persistent grid of the forward kernels (0: one block per logical block)
   int conv_split = 1;             // grid 0: central tiles in the lean convective sweep
+  bool om_tab = false;            // the mechanism's collision integral is tabulated
   htr_scheme scheme{};
   long long total_cells = 0;
   int n1[3] = {1, 1, 1};          // grid of the single-member case (laser normalisation)
@@ -147,6 +148,7 @@ inline TapeView tape_view(void* tape, int ns, long long N, int k) {
 struct htr_ctx {
   int device = 0;
   int ns = 0, nr = 0;
+  bool om_tab = false;             // the mechanism's collision integral is tabulated
   htr_scheme scheme{};
   htr::MechTables* dM = nullptr;   // device tables
   htr::Member host_mem{};          // single member (host copy)

@@ -27,18 +27,79 @@ __device__ __forceinline__ double hRT(const MechTables* __restrict__ M, int s, d
   const double* a = M->hc[s];
   return a[0] + T * (a[1] + T * (a[2] + T * (a[3] + T * a[4]))) + a[5] * iT;
 }
-__device__ __forceinline__ double sR(const MechTables* __restrict__ M, int s, double T, double lnT) {
-  const double* a = M->sc[s];
-  return a[0] * lnT + T * (a[1] + T * (a[2] + T * (a[3] + T * a[4]))) + a[5];
+// exp(x) for |x| up to 1e6 (2^n saturates to 0 or infinity): x = n ln 2 + r, |r| <= ln 2 / 2, and
+// exp(r) = 1 + r + r^2 q(r), q the degree-9 interpolant of (exp(r) - 1 - r) / r^2
+// at Chebyshev nodes (remainder 2e-17).  18 vector instructions; the general
+// library function spends about ten more on the ends of the range.
+__device__ __forceinline__ double exp_in(double x) {
+  const double n = rint(x * 1.4426950408889634074);
+  double r = fma(n, -0.69314718055994530942, x);
+  r = fma(n, -2.3190468138462995584e-17, r);
+  double q = 2.510038549551032e-08;
+  q = fma(q, r, 2.7620088445409746e-07);
+  q = fma(q, r, 2.7557268459997064e-06);
+  q = fma(q, r, 2.4801521295954376e-05);
+  q = fma(q, r, 0.00019841269863053618);
+  q = fma(q, r, 0.0013888888917213717);
+  q = fma(q, r, 0.008333333333330062);
+  q = fma(q, r, 0.04166666666662413);
+  q = fma(q, r, 0.16666666666666669);
+  q = fma(q, r, 0.5000000000000001);
+  return __builtin_ldexp(1.0 + fma(r * r, q, r), (int)n);
 }
 
-// Neufeld-Janzen-Aziz collision integrals; x = ln T - ln(eps/k), Ts = T/(eps/k).
-__device__ __forceinline__ double om22(double x, double Ts) {
-  return 1.16145 * exp(-0.14874 * x) + 0.52487 * exp(-0.77320 * Ts) + 2.16178 * exp(-2.43787 * Ts);
+// The same for any x (0 and infinity at the ends, infinity for NaN: a rate
+// constant's two sides then give NaN).
+__device__ __forceinline__ double exp_sat(double x) { return exp_in(fmax(fmin(x, 1e4), -1e4)); }
+
+// 1/x and 1/sqrt(x) of normal positive x: the hardware estimate and two
+// Newton steps (the last residual is formed with one rounding, so the result
+// is within an ulp).
+__device__ __forceinline__ double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
 }
-__device__ __forceinline__ double om11(double x, double Ts) {
-  return 1.06036 * exp(-0.15610 * x) + 0.19300 * exp(-0.47635 * Ts) + 1.03587 * exp(-1.52996 * Ts) +
-         1.76474 * exp(-3.89411 * Ts);
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-(x * y), y, 1.0), y);
+  return fma(0.5 * y, fma(-(x * y), y, 1.0), y);
+}
+
+// The species pairs i < j.
+template <int NS>
+struct Pairs {
+  static constexpr int N = NS * (NS - 1) / 2;
+  int i[N + 1] = {}, j[N + 1] = {};
+  constexpr Pairs() {
+    int p = 0;
+    for (int a = 0; a < NS; ++a)
+      for (int b = a + 1; b < NS; ++b, ++p) {
+        i[p] = a;
+        j[p] = b;
+      }
+  }
+};
+constexpr int OMPF = 3;
+// Neufeld-Janzen-Aziz collision integral Omega11(T*): from the staged table
+// (row = the top bits of T*, a polynomial in T* - the interval's centre), or
+// the fit itself.  The table's eight coefficients are four 16-byte LDS reads
+// and seven FMAs where the fit takes four exponentials.
+template <bool TAB>
+__device__ __forceinline__ double omega11(const double* __restrict__ s_om, int row0, int rows, double Ts) {
+  if constexpr (TAB) {
+    const int hi = __double2hiint(Ts);
+    const unsigned row = min((unsigned)((hi >> 15) - row0), (unsigned)(rows - 1));
+    const double t = Ts - __hiloint2double((hi & (int)0xffff8000) | 0x4000, 0);
+    const double* c = s_om + row * (OMDEG + 1);
+    double v = c[OMDEG];
+#pragma unroll
+    for (int k = OMDEG - 1; k >= 0; --k) v = fma(v, t, c[k]);
+    return v;
+  } else {
+    return 1.06036 * exp(-0.15610 * log(Ts)) + 0.19300 * exp(-0.47635 * Ts) + 1.03587 * exp(-1.52996 * Ts) +
+           1.76474 * exp(-3.89411 * Ts);
+  }
 }
 
 __device__ __forceinline__ double laser_axis(const LaserDev& L, const Member& G, int a, int i) {
@@ -133,16 +194,17 @@ __global__ __launch_bounds__(BLK) void k_prim_to_cons(const MechTables* __restri
 // One logical block bl of 256 cells.
 // CURV: curvilinear single grid (laser over lattice images, contravariant
 // dt limit, cell volume 1/J from the metric terms in cg).
-template <int NS, bool CURV>
+// TAB: Omega11 from the table s_om that the kernel staged in LDS.
+template <int NS, bool CURV, bool TAB>
 __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict__ M,
-                                            const Member* __restrict__ mem, int nmem, const CallArgs& A,
+                                            const Member* __restrict__ mem, int nmem, const CallArgs& A_,
                                             const double* __restrict__ Ub, double* __restrict__ Tb,
                                             double* __restrict__ auxb, double* __restrict__ srcb,
                                             double* __restrict__ hrrb, double* __restrict__ blkred,
                                             double* __restrict__ cellsb, unsigned* __restrict__ status,
-                                            int want_dt, const CurvGeom& cg) {
+                                            int want_dt, const CurvGeom& cg, const double* __restrict__ s_om) {
   constexpr int NV = NS + 4, NAUX = 7 + NS;
-  __shared__ double conc[NS][BLK];
+  __shared__ double conc[NS + 1][BLK];   // concentrations; the last row is the factor one
   __shared__ double wred[2][BLK / 64];
   const int m = find_member(mem, nmem, bl);
   const Member& G = mem[m];
@@ -150,7 +212,7 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
   const long long q = (long long)(bl - G.block_begin) * BLK + tid;
   const bool live = q < G.N;
   const long long N = G.N;
-  const unsigned flags = A.flags;
+  const unsigned flags = A_.flags;
   double hdv = 0.0, lim = INFINITY;
   if (live) {
     const double* U = Ub + NV * G.off;
@@ -158,6 +220,7 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     double* src = srcb + (NS + 1) * G.off;
     double r[NS], Y[NS];
     double rho = 0.0;
+    conc[NS][tid] = 1.0;
     bool finite = true;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -177,32 +240,34 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     for (int s = 0; s < NS; ++s) Y[s] = r[s] * irho;
     const double u = mx * irho, v = my * irho, w = mz * irho;
     const double e = E * irho - 0.5 * (u * u + v * v + w * w);
-    // temperature: Newton on e(T) = sum_s Y_s (h_s - R_u T / W_s); converge, then one more step
+    // temperature: Newton on e(T) = sum_s Y_s (h_s - R_u T / W_s); converge, then
+    // one more step.  The mixture's polynomial is formed once (sum_s Y_s R_u/W_s
+    // times each coefficient), so an iteration costs two Horner chains.
+    double A[6], Rm = 0.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) A[k] = 0.0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const double yr = Y[s] * M->RW[s];
+      Rm += yr;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) A[k] = fma(yr, M->cp[s][k], A[k]);
+      A[5] = fma(yr, M->hc[s][5], A[5]);
+    }
+    auto cp_mix = [&](double T) { return A[0] + T * (A[1] + T * (A[2] + T * (A[3] + T * A[4]))); };
     double T = Tb[G.off + q];
     bool conv = false;
     if (!err) {
+      const double H0 = A[0], H1 = A[1] / 2.0, H2 = A[2] / 3.0, H3 = A[3] / 4.0, H4 = A[4] / 5.0, e0 = A[5] - e;
+      auto newton = [&](double T) {
+        return (T * (H0 + T * (H1 + T * (H2 + T * (H3 + T * H4)))) - Rm * T + e0) * rcp_nr(cp_mix(T) - Rm);
+      };
       for (int it = 0; it < 50; ++it) {
-        const double iT = 1.0 / T;
-        double eT = 0.0, cv = 0.0;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const double yr = Y[s] * M->RW[s];
-          eT += yr * T * (hRT(M, s, T, iT) - 1.0);
-          cv += yr * (cpR(M, s, T) - 1.0);
-        }
-        const double dT = (eT - e) / cv;
+        const double dT = newton(T);
         T -= dT;
         if (!isfinite(T) || !(T > 0.0)) break;
         if (fabs(dT) <= 1e-12 * fabs(T)) {
-          const double iT2 = 1.0 / T;
-          double eT2 = 0.0, cv2 = 0.0;
-#pragma unroll
-          for (int s = 0; s < NS; ++s) {
-            const double yr = Y[s] * M->RW[s];
-            eT2 += yr * T * (hRT(M, s, T, iT2) - 1.0);
-            cv2 += yr * (cpR(M, s, T) - 1.0);
-          }
-          T -= (eT2 - e) / cv2;
+          T -= newton(T);
           conv = true;
           break;
         }
@@ -216,12 +281,10 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     }
     Tb[G.off + q] = T;
     const double iT = 1.0 / T;
-    double iWm = 0.0, cp = 0.0;
+    double iWm = 0.0;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      iWm += Y[s] * M->iW[s];
-      cp += Y[s] * M->RW[s] * cpR(M, s, T);
-    }
+    for (int s = 0; s < NS; ++s) iWm += Y[s] * M->iW[s];
+    const double cp = cp_mix(T);
     const double Wm = 1.0 / iWm;
     const double p = rho * RU * T * iWm;
     const double c = sqrt(cp / (cp - RU * iWm) * p * irho);
@@ -234,34 +297,39 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 #pragma unroll
     for (int s = 0; s < NS; ++s) X[s] = Y[s] * Wm * M->iW[s];
 
-    // ---- transport.  The power terms of the collision integrals factor:
-    // (T/eps)^-b = T^-b eps^b, one exponential per cell for each fit.
+    // ---- transport.  The power term of Omega22 factors: (T/eps)^-b = T^-b eps^b,
+    // one exponential per cell.  Wilke's phi_ij = (1 + sigma_i / sigma_j)^2 / sqrt(8 (1 + W_i / W_j))
+    // with sigma = sqrt(mu) W^(-1/4), so (sigma_i + sigma_j)^2 serves both i and j.
     const double lnT = log(T), sqT = sqrt(T);
-    const double Tb22 = exp(-0.14874 * lnT), Tb11 = exp(-0.15610 * lnT);
-    // (lambda_s and sqrt(mu_s) are formed where they are used, so that only
-    // mu_s and 1/sqrt(mu_s) are held for all species)
-    double mus[NS], ismu[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const double Ts = T * M->ieps[s];
-      const double o22 = 1.16145 * (Tb22 * M->pw22[s]) + 0.52487 * exp(-0.77320 * Ts) + 2.16178 * exp(-2.43787 * Ts);
-      mus[s] = M->mu_pre[s] * sqT / o22;
-      ismu[s] = 1.0 / sqrt(mus[s]);
-    }
     double mu = 0.0, lam = 0.0;
+    {
+      auto expT = [](double x) { return TAB ? exp_in(x) : exp(x); };   // T* below 1e6 where tabulated
+      const double Tb22 = exp_in(-0.14874 * lnT), isqT = rcp_nr(sqT);
+      double sg[NS], Z[NS], den[NS];
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-      const double smu = sqrt(mus[i]);
-      double den = 0.0;
-#pragma unroll
-      for (int j = 0; j < NS; ++j) {
-        const double t1 = 1.0 + smu * ismu[j] * M->wq[i][j];
-        den += X[j] * (t1 * t1 * M->wp[i][j]);
+      for (int s = 0; s < NS; ++s) {
+        const double Ts = T * M->ieps[s];
+        const double o22 = 1.16145 * (Tb22 * M->pw22[s]) + 0.52487 * expT(-0.77320 * Ts) + 2.16178 * expT(-2.43787 * Ts);
+        const double imu = o22 * (M->imu_pre[s] * isqT);
+        sg[s] = rsqrt_nr(imu) * M->qW[s];
+        Z[s] = X[s] * (imu * M->rsW[s]);
+        den[s] = X[s];
       }
-      const double id = 1.0 / den;
-      const double lams = mus[i] * (M->RW[i] * cpR(M, i, T) + M->euck[i]);
-      mu += X[i] * mus[i] * id;
-      lam += X[i] * lams * id;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+#pragma unroll
+        for (int j = i + 1; j < NS; ++j) {
+          const double t1 = sg[i] + sg[j], t2 = t1 * t1;
+          den[i] = fma(Z[j] * M->wp[i][j], t2, den[i]);
+          den[j] = fma(Z[i] * M->wp[j][i], t2, den[j]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        const double xm = X[i] * (sg[i] * sg[i] * M->rsW[i]) * rcp_nr(den[i]);
+        mu += xm;
+        lam += xm * (M->RW[i] * cpR(M, i, T) + M->euck[i]);
+      }
     }
     aux[2 * N + q] = mu;
     aux[3 * N + q] = lam;
@@ -269,26 +337,42 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 #pragma unroll
     for (int s = 0; s < NS; ++s) Dacc[s] = 0.0;
     const double T15 = T * sqT, pT15 = p / T15;
+    const int omr0 = M->omrow0, omrs = M->omrows;
+    // the pairs (i < j) in groups of OMPF, each group's integrals formed before
+    // the next group's table rows are read: left alone, the compiler reads
+    // every pair's row first and spills 1.8 KB per lane
+    constexpr Pairs<NS> PR;
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
+    for (int p0 = 0; p0 < Pairs<NS>::N; p0 += OMPF) {
+      double iD[OMPF];
 #pragma unroll
-      for (int j = i + 1; j < NS; ++j) {
-        const double Ts = T * M->Dieps[i][j];
-        const double o11 = 1.06036 * (Tb11 * M->pw11[i][j]) + 0.19300 * exp(-0.47635 * Ts) +
-                           1.03587 * exp(-1.52996 * Ts) + 1.76474 * exp(-3.89411 * Ts);
-        const double iD = pT15 * o11 * M->iDpre[i][j];
-        Dacc[i] += fmax(X[j], 0.0) * iD;
-        Dacc[j] += fmax(X[i], 0.0) * iD;
-      }
+      for (int k = 0; k < OMPF; ++k)
+        if (p0 + k < Pairs<NS>::N)
+          iD[k] = omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[PR.i[p0 + k]][PR.j[p0 + k]]);
+#pragma unroll
+      for (int k = 0; k < OMPF; ++k)
+        if (p0 + k < Pairs<NS>::N) asm volatile("" : "+v"(iD[k])::"memory");
+#pragma unroll
+      for (int k = 0; k < OMPF; ++k)
+        if (p0 + k < Pairs<NS>::N) {
+          const int i = PR.i[p0 + k], j = PR.j[p0 + k];
+          const double d = iD[k] * M->iDpre[i][j];
+          Dacc[i] += fmax(X[j], 0.0) * d;
+          Dacc[j] += fmax(X[i], 0.0) * d;
+        }
     }
+    bool pure = false;   // a species alone in the mixture takes its self-diffusivity
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      if (Dacc[s] < 1e-300) {
-        const double Ts = T * M->Dieps[s][s];
-        Ds[s] = M->Dpre[s][s] * T15 / (p * om11(lnT - M->Dlneps[s][s], Ts));
-      } else {
-        Ds[s] = (1.0 - Y[s]) / Dacc[s];
-      }
+      const double D = Dacc[s] * pT15;
+      pure = pure || D < 1e-300;
+      Ds[s] = (1.0 - Y[s]) * rcp_nr(D);
+    }
+    if (pure) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        if (Dacc[s] * pT15 < 1e-300)
+          Ds[s] = M->Dpre[s][s] * T15 / (p * omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[s][s]));
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) aux[(7 + s) * N + q] = Ds[s];
@@ -301,9 +385,12 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     if (!(flags & HTR_CHEM_OFF)) {
       double Gs[NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) Gs[s] = hRT(M, s, T, iT) - sR(M, s, T, lnT);
-      const double lnP = log(PREF / (RU * T));
-      const double* dlnA = A.dlnA ? A.dlnA : G.dlnA;
+      for (int s = 0; s < NS; ++s) {
+        const double* g = M->gc[s];   // h/(RT) - s/R
+        Gs[s] = g[0] - M->cp[s][0] * lnT + T * (g[1] + T * (g[2] + T * (g[3] + T * g[4]))) + g[5] * iT;
+      }
+      const double lnP = M->lnP0 - lnT;
+      const double* dlnA = A_.dlnA ? A_.dlnA : G.dlnA;
       const int nr = M->nr;
       for (int j = 0; j < nr; ++j) {
         double lnkf = M->lnA[j] + M->beta[j] * lnT - M->EaR[j] * iT;
@@ -311,14 +398,17 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
         double lnKc = M->dnu[j] * lnP;
 #pragma unroll
         for (int s = 0; s < NS; ++s) lnKc -= M->nunet[j][s] * Gs[s];
-        double rf = exp(lnkf), rb = exp(lnkf - lnKc);
-        for (int e = 0; e < M->nre[j]; ++e) {
-          const double cs = conc[M->ridx[j][e]][tid];
-          for (int k = 0; k < M->rnu[j][e]; ++k) rf *= cs;
+        // mass action: three factors a side (absent ones are one), more only
+        // where a side's order is higher
+        double rf = exp_sat(lnkf), rb = exp_sat(lnkf - lnKc);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          rf *= conc[M->rfac[j][e]][tid];
+          rb *= conc[M->pfac[j][e]][tid];
         }
-        for (int e = 0; e < M->npr[j]; ++e) {
-          const double cs = conc[M->pidx[j][e]][tid];
-          for (int k = 0; k < M->pnu[j][e]; ++k) rb *= cs;
+        for (int e = 3; e < M->nfac[j]; ++e) {
+          rf *= conc[M->rfac[j][e]][tid];
+          rb *= conc[M->pfac[j][e]][tid];
         }
         const double qj = rf - rb;
 #pragma unroll
@@ -332,10 +422,10 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     }
     // ---- laser
     const int i = (int)(q % G.n[0]), jj = (int)((q / G.n[0]) % G.n[1]), k = (int)(q / ((long long)G.n[0] * G.n[1]));
-    const LaserDev& L = A.use_call_laser ? A.laser : G.laser;
+    const LaserDev& L = A_.use_call_laser ? A_.laser : G.laser;
     double qL = 0.0;
     if (L.on) {
-      const double tk = (A.t_dev ? A.t_dev[m] : A.t) + (A.dt_dev ? A.tcoef * A.dt_dev[m] : 0.0);
+      const double tk = (A_.t_dev ? A_.t_dev[m] : A_.t) + (A_.dt_dev ? A_.tcoef * A_.dt_dev[m] : 0.0);
       const double tt = (tk - L.t0) / L.st;
       const double gs = CURV ? laser_curv(L, G, cg, q)
                              : laser_axis(L, G, 0, i) * laser_axis(L, G, 1, jj) * laser_axis(L, G, 2, k);
@@ -426,7 +516,13 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 
 // Grid-stride over the nlog logical blocks: one pass when the grid has one
 // block per logical block, persistent blocks when it has fewer.
-template <int NS, bool PERSIST, bool CURV>
+// Bound by FP64 instructions.  Tabulating Omega11 (36 pairs at nine species),
+// the mixture's polynomials in the Newton iteration, Wilke's pairs taken
+// once and the short exponentials brought it from 644 to 397 us at 128^3 cells,
+// nine species and twenty reactions (1257 to 740 us on the 256x128x128 mixing
+// layer); its bytes, read and written once, take 153 us at the 4.7 TB/s of a
+// large copy.
+template <int NS, bool PERSIST, bool CURV, bool TAB>
 __global__ __launch_bounds__(BLK, NS <= 9 ? 3 : 2) void k_point(const MechTables* __restrict__ M,
                                                                 const Member* __restrict__ mem, int nmem, int nlog,
                                                                 CallArgs A, const double* __restrict__ Ub,
@@ -436,13 +532,22 @@ __global__ __launch_bounds__(BLK, NS <= 9 ? 3 : 2) void k_point(const MechTables
                                                                 double* __restrict__ cellsb,
                                                                 unsigned* __restrict__ status, int want_dt,
                                                                 CurvGeom cg) {
+  __shared__ alignas(16) double s_om[TAB ? OMROWS * (OMDEG + 1) : 2];
+  if constexpr (TAB) {
+    const double2* from = reinterpret_cast<const double2*>(&M->om11[0][0]);
+    double2* to = reinterpret_cast<double2*>(s_om);
+    const int n2 = M->omrows * (OMDEG + 1) / 2;
+    for (int k = threadIdx.x; k < n2; k += BLK) to[k] = from[k];
+    __syncthreads();
+  }
   if (!PERSIST) {
-    point_block<NS, CURV>(blockIdx.x, M, mem, nmem, A, Ub, Tb, auxb, srcb, hrrb, blkred, cellsb, status, want_dt,
-                          cg);
+    point_block<NS, CURV, TAB>(blockIdx.x, M, mem, nmem, A, Ub, Tb, auxb, srcb, hrrb, blkred, cellsb, status, want_dt,
+                               cg, s_om);
     return;
   }
   for (int bl = blockIdx.x; bl < nlog; bl += gridDim.x) {
-    point_block<NS, CURV>(bl, M, mem, nmem, A, Ub, Tb, auxb, srcb, hrrb, blkred, cellsb, status, want_dt, cg);
+    point_block<NS, CURV, TAB>(bl, M, mem, nmem, A, Ub, Tb, auxb, srcb, hrrb, blkred, cellsb, status, want_dt, cg,
+                               s_om);
     __syncthreads();   // the next logical block reuses the LDS
   }
 }
@@ -581,21 +686,28 @@ static hipError_t prim_to_cons_t(const MechTables* M, const Member* mem, int nme
   return hipGetLastError();
 }
 
+// A mechanism without a table (om_tab false: a single species, or a range of
+// T* wider than the table holds) runs one block per logical block.
 template <int NS>
 static hipError_t point_t(const MechTables* M, const Member* mem, int nmem, int nblocks, int grid,
                           const CallArgs& a, const double* U, double* T, double* aux, double* src, double* hrr,
-                          double* blkred, double* cells, unsigned* status, int want_dt, hipStream_t s,
+                          double* blkred, double* cells, unsigned* status, int want_dt, bool om_tab, hipStream_t s,
                           const CurvGeom* cg) {
-  const CurvGeom none{};
-  if (cg)   // curvilinear single grid: one block per logical block
-    hipLaunchKernelGGL((k_point<NS, false, true>), dim3(nblocks), dim3(BLK), 0, s, M, mem, nmem, nblocks, a, U, T,
-                       aux, src, hrr, blkred, cells, status, want_dt, *cg);
-  else if (grid < nblocks)
-    hipLaunchKernelGGL((k_point<NS, true, false>), dim3(grid), dim3(BLK), 0, s, M, mem, nmem, nblocks, a, U, T, aux,
-                       src, hrr, blkred, cells, status, want_dt, none);
-  else
-    hipLaunchKernelGGL((k_point<NS, false, false>), dim3(grid), dim3(BLK), 0, s, M, mem, nmem, nblocks, a, U, T, aux,
-                       src, hrr, blkred, cells, status, want_dt, none);
+  const CurvGeom geom = cg ? *cg : CurvGeom{};
+#define P_(PERSIST, CURV, TAB, G)                                                                                  \
+  hipLaunchKernelGGL((k_point<NS, PERSIST, CURV, TAB>), dim3(G), dim3(BLK), 0, s, M, mem, nmem, nblocks, a, U, T, aux, \
+                     src, hrr, blkred, cells, status, want_dt, geom)
+  if (cg) {   // curvilinear single grid: one block per logical block
+    if (om_tab) P_(false, true, true, nblocks);
+    else P_(false, true, false, nblocks);
+  } else if (!om_tab) {
+    P_(false, false, false, nblocks);
+  } else if (grid < nblocks) {
+    P_(true, false, true, grid);
+  } else {
+    P_(false, false, true, nblocks);
+  }
+#undef P_
   return hipGetLastError();
 }
 
@@ -612,10 +724,10 @@ hipError_t launch_prim_to_cons(int ns, const MechTables* M, const Member* mem, i
 
 hipError_t launch_point(int ns, const MechTables* M, const Member* mem, int nmem, int nblocks, int grid,
                         const CallArgs& a, const double* U, double* T, double* aux, double* src, double* hrr,
-                        double* blkred, double* cells, unsigned* status, int want_dt, hipStream_t s,
+                        double* blkred, double* cells, unsigned* status, int want_dt, bool om_tab, hipStream_t s,
                         const CurvGeom* cg) {
   grid = grid_of(nblocks, grid);
-#define C_(NS) point_t<NS>(M, mem, nmem, nblocks, grid, a, U, T, aux, src, hrr, blkred, cells, status, want_dt, s, cg)
+#define C_(NS) point_t<NS>(M, mem, nmem, nblocks, grid, a, U, T, aux, src, hrr, blkred, cells, status, want_dt, om_tab, s, cg)
   HTR_NS_SWITCH(ns, C_)
 #undef C_
 }
