@@ -404,7 +404,7 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
     // the cells next to non-periodic boundaries: their whole right-hand side
     if (teno_bits) return fail(HTR_EUNSUPPORTED, "no tape on a grid with non-periodic boundaries");
     TimedLaunch tl(C.timer, TC_UPDATE, s);
-    HIP_OK(launch_bnd(C.ns, C.M, C.mem, C.nblocks, a, U, T, w.aux, w.src, w.flag, w.grad, w.part, C.scheme.psi_c,
+    HIP_OK(launch_bnd(C.ns, C.M, C.mem, *C.host1, a, U, T, w.aux, w.src, w.flag, w.grad, w.part, C.scheme.psi_c,
                       C.scheme.teno_CT, s));
   }
   {
@@ -476,10 +476,10 @@ Ctx htr::view(const htr_ctx* c) {
   }
   v.timer = const_cast<Timer*>(&c->timer);
   v.bounded = c->host_mem.bounded != 0;
+  v.host1 = &c->host_mem;
   if (c->curv) {
     const long long N = c->N;
     v.curv = &c->cg;
-    v.host1 = &c->host_mem;
     v.cX = c->dcw;
     v.cdphi = c->dcw + (long long)c->ns * N;
     v.cffc = v.cdphi + 3LL * (4 + c->ns) * N;

@@ -247,8 +247,8 @@ hipError_t launch_conv(int ns, const MechTables* M, const Member* mem, int nmem,
                        const double* U, const double* aux, const double* src, const unsigned char* flag, double* part,
                        unsigned char* bits, double psi_c, double CT, unsigned char* tcls, hipStream_t s);
 // Right-hand side of the cells next to non-periodic boundaries (single
-// grid), written over the convective sweep's part[] for those cells.
-hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, int nblocks, const CallArgs& a, const double* U,
+// grid, host its member on the host), written over the convective sweep's part[] for those cells.
+hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, const Member& host, const CallArgs& a, const double* U,
                       const double* T, const double* aux, const double* src, const unsigned char* flag,
                       const double* grad, double* part, double psi_c, double CT, hipStream_t s);
 hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid,

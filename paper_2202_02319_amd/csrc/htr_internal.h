@@ -98,7 +98,7 @@ struct Ctx {
   bool bounded = false;           // single grid with non-periodic boundaries (boundary kernel)
   // curvilinear single grid (null: rectilinear sweeps)
   const CurvGeom* curv = nullptr;
-  const Member* host1 = nullptr;  // host copy of the single member (curvilinear launch shapes)
+  const Member* host1 = nullptr;  // host copy of the single member (launch shapes of curvilinear and bounded grids)
   double* cX = nullptr;           // [ns][N] mole fractions
   double* cdphi = nullptr;        // [3][4 + ns][N] index-space central differences
   double* cffc = nullptr;         // [3][ns + 4][N] mapped convective face fluxes

@@ -720,8 +720,8 @@ __global__ __launch_bounds__(BLKF, 3) void k_diff(const MechTables* __restrict__
 
 // ----------------------------------------------------- non-periodic boundaries
 // Cells within three nodes of a bounded boundary (in_boundary_slab) get
-// their whole right-hand side here, one thread per cell, evaluating each of
-// their faces on its own (the tiled sweeps assume periodic wrap).  On a
+// their whole right-hand side here, each cell's faces evaluated on their own
+// (the tiled sweeps assume periodic wrap).  On a
 // bounded axis the first and last nodes lie on the boundary; a face whose
 // six-point stencil does not fit takes the widest centred interpolation that
 // does ((-1, 7, 7, -1)/12 or (1, 1)/2), or, where the hybrid switch marks
@@ -734,78 +734,79 @@ __global__ __launch_bounds__(BLKF, 3) void k_diff(const MechTables* __restrict__
 // and T, inflows also Y, with the entering acoustic wave equal to the
 // leaving one; Methods › Model rocket combustor › Numerical setup).
 
+constexpr int BNDC = 64;   // slab cells of a block: one wavefront per face
+
 __device__ __forceinline__ double cpR_b(const MechTables* __restrict__ M, int s, double T) {
   const double* a = M->cp[s];
   return a[0] + T * (a[1] + T * (a[2] + T * (a[3] + T * a[4])));
 }
 
-// Linear index of node k along axis d of the stencil through cell c
-// (periodic axes wrap).
-__device__ __forceinline__ long long node_along(const Member& G, const int c[3], int d, int k) {
-  int g[3] = {c[0], c[1], c[2]};
-  g[d] = G.bc[d][0] != 0 ? k : wrapi(k, G.n[d]);
-  return lin(G, g);
-}
-
 // Convective flux through face i+1/2 along d (i = c[d] with the other
-// coordinates of c), every variable, into out[].
+// coordinates of c), variable by variable, into out[v * BNDC].  The six slots
+// of the full stencil are all loaded (on a bounded axis clamped to the grid);
+// a face of m < 6 points uses the middle m of them.
 template <int NS>
-__device__ void bnd_conv_face(const Member& G, int d, const int c[3], const double* __restrict__ U,
-                              const double* __restrict__ aux, const unsigned char* __restrict__ flag, unsigned flags,
-                              double psi_c, double CT, double* out) {
+__device__ __forceinline__ void bnd_conv_face(const Member& G, int d, const int c[3], const double* __restrict__ U,
+                                              const double* __restrict__ aux, const unsigned char* __restrict__ flag,
+                                              unsigned flags, double psi_c, double CT, double* out) {
   constexpr int NV = NS + 4;
   const long long N = G.N;
   const int i = c[d], n = G.n[d];
-  int m = 6, start = i - 2;
-  if (G.bc[d][0] != 0 && (i < 2 || i > n - 4)) {
-    m = (i == 0 || i == n - 2) ? 2 : 4;
-    start = i - m / 2 + 1;
-  }
+  const bool bnd = G.bc[d][0] != 0;
+  const int m = !bnd || (i >= 2 && i <= n - 4) ? 6 : ((i == 0 || i == n - 2) ? 2 : 4);
+  const int lo = (6 - m) / 2;
   long long st[6];
-  for (int k = 0; k < m; ++k) st[k] = node_along(G, c, d, start + k);
-  const int fa = m / 2 - 1, fb = m / 2;   // the face's two nodes
+  double ud[6], p[6];
+  double al = 0.0;
+  int any = 0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    int g[3] = {c[0], c[1], c[2]};
+    const int j = i - 2 + k;
+    const int w = bnd ? (j < 0 ? 0 : (j >= n ? n - 1 : j)) : wrapi(j, n);
+    g[0] = d == 0 ? w : g[0];
+    g[1] = d == 1 ? w : g[1];
+    g[2] = d == 2 ? w : g[2];
+    st[k] = lin(G, g);
+    ud[k] = aux[(4 + d) * N + st[k]];
+    p[k] = aux[st[k]];
+    if (k >= lo && k < 6 - lo) {
+      any |= flag[st[k]];
+      al = fmax(al, fabs(ud[k]) + aux[N + st[k]]);
+    }
+  }
   bool te;
   if (flags & HTR_FORCE_TENO) te = true;
   else if (flags & HTR_FORCE_CENTRAL) te = false;
-  else {
-    int any = 0;
-    for (int k = 0; k < m; ++k) any |= flag[st[k]];
-    const double pa = aux[st[fa]], pb = aux[st[fb]];
-    te = any != 0 || fabs(pb - pa) / fmin(pa, pb) > psi_c;
-  }
-  double ud[6], p[6];
-  for (int k = 0; k < m; ++k) {
-    ud[k] = aux[(4 + d) * N + st[k]];
-    p[k] = aux[st[k]];
-  }
-  double al = 0.0;
-  if (te) {
-    al = fabs(ud[0]) + aux[N + st[0]];
-    for (int k = 1; k < m; ++k) al = fmax(al, fabs(ud[k]) + aux[N + st[k]]);
-  }
+  else te = any != 0 || fabs(p[3] - p[2]) / fmin(p[2], p[3]) > psi_c;
+#pragma unroll 1
   for (int v = 0; v < NV; ++v) {
     double u6[6], f6[6];
-    for (int k = 0; k < m; ++k) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
       u6[k] = U[v * N + st[k]];
       f6[k] = node_flux<NS>(v, d, u6[k], ud[k], p[k]);
     }
+    double f;
     if (!te) {
       if (m == 6)
-        out[v] = (f6[0] - 8.0 * f6[1] + 37.0 * f6[2] + 37.0 * f6[3] - 8.0 * f6[4] + f6[5]) * (1.0 / 60.0);
+        f = (f6[0] - 8.0 * f6[1] + 37.0 * f6[2] + 37.0 * f6[3] - 8.0 * f6[4] + f6[5]) * (1.0 / 60.0);
       else if (m == 4)
-        out[v] = (-f6[0] + 7.0 * f6[1] + 7.0 * f6[2] - f6[3]) * (1.0 / 12.0);
+        f = (-f6[1] + 7.0 * f6[2] + 7.0 * f6[3] - f6[4]) * (1.0 / 12.0);
       else
-        out[v] = 0.5 * (f6[0] + f6[1]);
+        f = 0.5 * (f6[2] + f6[3]);
     } else if (m == 6) {
       double hp[6], hm[6];
+#pragma unroll
       for (int k = 0; k < 6; ++k) {
         hp[k] = fma(al, u6[k], f6[k]);
         hm[5 - k] = fma(-al, u6[k], f6[k]);
       }
-      out[v] = (flags & HTR_WENO3Z) ? weno3z_h(hp) + weno3z_h(hm) : teno6_h(hp, CT) + teno6_h(hm, CT);
+      f = (flags & HTR_WENO3Z) ? weno3z_h(hp) + weno3z_h(hm) : teno6_h(hp, CT) + teno6_h(hm, CT);
     } else {
-      out[v] = 0.5 * (f6[fa] + f6[fb]) - 0.5 * al * (u6[fb] - u6[fa]);
+      f = 0.5 * (f6[2] + f6[3]) - 0.5 * al * (u6[3] - u6[2]);
     }
+    out[v * BNDC] = f;
   }
 }
 
@@ -814,65 +815,126 @@ __device__ __forceinline__ void bnd_diff_face(const MechTables* __restrict__ M, 
                                               const double* __restrict__ U, const double* __restrict__ T,
                                               const double* __restrict__ aux, const double* __restrict__ grad,
                                               double* out) {
-  int cb[3] = {c[0], c[1], c[2]};
-  cb[d] = G.bc[d][0] != 0 ? c[d] + 1 : wrapi(c[d] + 1, G.n[d]);
+  const int w = G.bc[d][0] != 0 ? c[d] + 1 : wrapi(c[d] + 1, G.n[d]);
+  const int cb[3] = {d == 0 ? w : c[0], d == 1 ? w : c[1], d == 2 ? w : c[2]};
   const long long qA = lin(G, c), qB = lin(G, cb);
-  if (d == 0) diff_face<NS, 0>(M, G, c[0], qA, qB, G.N, U, T, aux, grad, out);
-  else if (d == 1) diff_face<NS, 1>(M, G, c[1], qA, qB, G.N, U, T, aux, grad, out);
-  else diff_face<NS, 2>(M, G, c[2], qA, qB, G.N, U, T, aux, grad, out);
+  double fd[NS + 4];
+  if (d == 0) diff_face<NS, 0>(M, G, c[0], qA, qB, G.N, U, T, aux, grad, fd);
+  else if (d == 1) diff_face<NS, 1>(M, G, c[1], qA, qB, G.N, U, T, aux, grad, fd);
+  else diff_face<NS, 2>(M, G, c[2], qA, qB, G.N, U, T, aux, grad, fd);
+#pragma unroll
+  for (int v = 0; v < NS + 4; ++v) out[v * BNDC] = fd[v];
 }
 
+// The slab cells in a dense order: axis by axis the six layers next to its
+// two sides (the layer fastest on x, x otherwise), without the layers of the
+// bounded axes before it.  Cells of axis a's part:
+__host__ __device__ inline long long slab_cells(const int n[3], const int bc[3][2], int a) {
+  if (bc[a][0] == 0) return 0;
+  long long k = 6;
+  for (int b = 0; b < 3; ++b)
+    if (b != a) k *= n[b] - (b < a && bc[b][0] != 0 ? 6 : 0);
+  return k;
+}
+__device__ __forceinline__ bool slab_cell(const Member& G, long long k, int c[3]) {
+  int a = 0;
+  for (; a < 3; ++a) {
+    const long long m = slab_cells(G.n, G.bc, a);
+    if (k < m) break;
+    k -= m;
+  }
+  if (a == 3) return false;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) {
+    const bool in = b < a && G.bc[b][0] != 0;   // inside the earlier axes' layers
+    const int ext = b == a ? 6 : G.n[b] - (in ? 6 : 0);
+    const int r = (int)(k % ext);
+    k /= ext;
+    c[b] = b == a ? (r < 3 ? r : G.n[b] - 6 + r) : (in ? r + 3 : r);
+  }
+  return true;
+}
+
+// One block: BNDC slab cells by six waves, wave r evaluating face r of every
+// cell (axis r / 2, upper face when r is even), so the axis is uniform in a
+// wave and a cell's faces are evaluated side by side; convective and
+// diffusive fluxes pass through LDS in turn.  Bound by one wave's chain of
+// thirteen TENO faces.  One thread per grid cell (a few active lanes in each
+// wave, each with all of its cell's faces in turn, 456 registers) took 1554 us on
+// 100x72x48 cells with two bounded axes (14% of them in the slab); this order
+// takes 176 us (252 registers and no scratch, one block per CU: 180 us).
 template <int NS>
-__global__ __launch_bounds__(BLK) void k_bnd(const MechTables* __restrict__ M, const Member* __restrict__ mem,
-                                             CallArgs A, const double* __restrict__ U, const double* __restrict__ T,
-                                             const double* __restrict__ aux, const double* __restrict__ src,
-                                             const unsigned char* __restrict__ flag,
-                                             const double* __restrict__ grad, double* __restrict__ part,
-                                             double psi_c, double CT) {
-  constexpr int NV = NS + 4;
+__global__ __launch_bounds__(6 * BNDC, 3) void k_bnd(const MechTables* __restrict__ M, const Member* __restrict__ mem,
+                                                  CallArgs A, const double* __restrict__ U,
+                                                  const double* __restrict__ T, const double* __restrict__ aux,
+                                                  const double* __restrict__ src,
+                                                  const unsigned char* __restrict__ flag,
+                                                  const double* __restrict__ grad, double* __restrict__ part,
+                                                  double psi_c, double CT) {
+  constexpr int NV = NS + 4, VPT = (NV + 5) / 6;
+  __shared__ double s_f[6][NV][BNDC], s_acc[NV][BNDC];
   const Member& G = mem[0];
-  const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
-  if (q >= G.N) return;
   const long long N = G.N;
-  const int c[3] = {(int)(q % G.n[0]), (int)((q / G.n[0]) % G.n[1]), (int)(q / ((long long)G.n[0] * G.n[1]))};
-  if (!in_boundary_slab(G, c)) return;
+  const int lane = threadIdx.x % BNDC, role = __builtin_amdgcn_readfirstlane(threadIdx.x / BNDC);
+  int c[3] = {0, 0, 0};
+  const bool valid = slab_cell(G, (long long)blockIdx.x * BNDC + lane, c);
+  const long long q = lin(G, c);
   const unsigned flags = A.flags;
+  const int a = role / 2;
+  const bool lower = role & 1;
+  bool edge[3];   // on that axis's boundary
+#pragma unroll
+  for (int b = 0; b < 3; ++b) edge[b] = G.act[b] && G.bc[b][0] != 0 && (c[b] == 0 || c[b] == G.n[b] - 1);
+  // this thread's face: its lower node
+  int cf[3] = {c[0], c[1], c[2]};
+  if (lower) {
+    const int ca = a == 0 ? c[0] : (a == 1 ? c[1] : c[2]);
+    const int w = G.bc[a][0] != 0 ? ca - 1 : wrapi(ca - 1, G.n[a]);
+    cf[0] = a == 0 ? w : cf[0];
+    cf[1] = a == 1 ? w : cf[1];
+    cf[2] = a == 2 ? w : cf[2];
+  }
+  const bool on_edge = a == 0 ? edge[0] : (a == 1 ? edge[1] : edge[2]);
+  const bool inner = valid && G.act[a] && !on_edge;
+  if (inner) bnd_conv_face<NS>(G, a, cf, U, aux, flag, flags, psi_c, CT, &s_f[role][0][lane]);
+  __syncthreads();
+  // variables role, role + 6, ...: the convective differences
+  double cd[3][VPT];
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    const int v = role + 6 * k;
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+      cd[b][k] = v < NV && G.act[b] && !edge[b] ? s_f[2 * b][v][lane] - s_f[2 * b + 1][v][lane] : 0.0;
+  }
+  __syncthreads();
+  // the face inside the domain of a wall node too: the wall's species diffusion
+  const int side_a = (a == 0 ? c[0] : (a == 1 ? c[1] : c[2])) == 0 ? 0 : 1;
+  const bool wall_in = valid && on_edge && G.bc[a][side_a] == HTR_BC_WALL && (side_a == 1) == lower;
+  if (!(flags & HTR_VISC_OFF) && (inner || wall_in))
+    bnd_diff_face<NS>(M, G, a, cf, U, T, aux, grad, &s_f[role][0][lane]);
+  __syncthreads();
+  const bool onb = edge[0] || edge[1] || edge[2];
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    const int v = role + 6 * k;
+    if (!valid || v >= NV) continue;
+    double r = v < NS ? src[v * N + q] : (v == NS + 3 ? src[NS * N + q] : 0.0);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      if (!G.act[b] || edge[b]) continue;
+      const double fd = flags & HTR_VISC_OFF ? 0.0 : s_f[2 * b][v][lane] - s_f[2 * b + 1][v][lane];
+      r += G.xin[b][c[b]] * (fd - cd[b][k]);
+    }
+    if (onb) s_acc[v][lane] = r;
+    else part[v * N + q] = r;
+  }
+  __syncthreads();
+  if (role != 0 || !valid || !onb) return;
   double acc[NV];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) acc[v] = v < NS ? src[v * N + q] : (v == NS + 3 ? src[NS * N + q] : 0.0);
-  bool onb = false;
-  double fdw[3][NS];   // diffusive species flux of the face next to a wall node, per axis
-  for (int a = 0; a < 3; ++a) {
-    if (!G.act[a]) continue;
-    const bool bnd = G.bc[a][0] != 0;
-    const bool edge = bnd && (c[a] == 0 || c[a] == G.n[a] - 1);
-    onb = onb || edge;
-    if (edge) {
-      // the node's face inside the domain, for a wall's species diffusion
-      if (!(flags & HTR_VISC_OFF) && (G.bc[a][c[a] == 0 ? 0 : 1] == HTR_BC_WALL)) {
-        int cf[3] = {c[0], c[1], c[2]};
-        if (c[a] != 0) cf[a] -= 1;
-        double fd[NV];
-        bnd_diff_face<NS>(M, G, a, cf, U, T, aux, grad, fd);
-        for (int s = 0; s < NS; ++s) fdw[a][s] = fd[s];
-      }
-      continue;
-    }
-    int cm[3] = {c[0], c[1], c[2]};
-    cm[a] = bnd ? c[a] - 1 : wrapi(c[a] - 1, G.n[a]);
-    double fcp[NV], fcm[NV], fdp[NV], fdm[NV];
-    bnd_conv_face<NS>(G, a, c, U, aux, flag, flags, psi_c, CT, fcp);
-    bnd_conv_face<NS>(G, a, cm, U, aux, flag, flags, psi_c, CT, fcm);
-    if (flags & HTR_VISC_OFF) {
-      for (int v = 0; v < NV; ++v) fdp[v] = fdm[v] = 0.0;
-    } else {
-      bnd_diff_face<NS>(M, G, a, c, U, T, aux, grad, fdp);
-      bnd_diff_face<NS>(M, G, a, cm, U, T, aux, grad, fdm);
-    }
-    const double xi = G.xin[a][c[a]];
-    for (int v = 0; v < NV; ++v) acc[v] += xi * ((fdp[v] - fdm[v]) - (fcp[v] - fcm[v]));
-  }
-  if (onb) {
+  for (int v = 0; v < NV; ++v) acc[v] = s_acc[v][lane];
+  {
     // boundary node: characteristic treatment along every bounded axis it lies on
     double Y[NS], rho = 0.0;
     for (int s = 0; s < NS; ++s) rho += U[s * N + q];
@@ -924,7 +986,7 @@ __global__ __launch_bounds__(BLK) void k_bnd(const MechTables* __restrict__ M, c
         for (int s = 0; s < NS; ++s) add[s] += Y[s] * drho;
         if (type == HTR_BC_WALL && !(flags & HTR_VISC_OFF)) {
           const double x2 = 2.0 * xi;
-          for (int s = 0; s < NS; ++s) add[s] += (side ? -x2 : x2) * fdw[a][s];
+          for (int s = 0; s < NS; ++s) add[s] += (side ? -x2 : x2) * s_f[2 * a + side][s][lane];
         }
         continue;
       }
@@ -982,17 +1044,20 @@ __global__ __launch_bounds__(BLK) void k_bnd(const MechTables* __restrict__ M, c
 }
 
 template <int NS>
-static hipError_t bnd_t(const MechTables* M, const Member* mem, int nblocks, const CallArgs& a, const double* U,
+static hipError_t bnd_t(const MechTables* M, const Member* mem, const Member& host, const CallArgs& a, const double* U,
                         const double* T, const double* aux, const double* src, const unsigned char* flag,
                         const double* grad, double* part, double psi_c, double CT, hipStream_t s) {
-  hipLaunchKernelGGL(k_bnd<NS>, dim3(nblocks), dim3(BLK), 0, s, M, mem, a, U, T, aux, src, flag, grad, part, psi_c, CT);
+  long long cells = 0;
+  for (int b = 0; b < 3; ++b) cells += slab_cells(host.n, host.bc, b);
+  const unsigned nblocks = (unsigned)((cells + BNDC - 1) / BNDC);
+  hipLaunchKernelGGL(k_bnd<NS>, dim3(nblocks), dim3(6 * BNDC), 0, s, M, mem, a, U, T, aux, src, flag, grad, part, psi_c, CT);
   return hipGetLastError();
 }
 
-hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, int nblocks, const CallArgs& a, const double* U,
+hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, const Member& host, const CallArgs& a, const double* U,
                       const double* T, const double* aux, const double* src, const unsigned char* flag,
                       const double* grad, double* part, double psi_c, double CT, hipStream_t s) {
-#define C_(NS) bnd_t<NS>(M, mem, nblocks, a, U, T, aux, src, flag, grad, part, psi_c, CT, s)
+#define C_(NS) bnd_t<NS>(M, mem, host, a, U, T, aux, src, flag, grad, part, psi_c, CT, s)
   HTR_NS_SWITCH(ns, C_);
 #undef C_
 }
