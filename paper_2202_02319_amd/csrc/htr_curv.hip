@@ -253,6 +253,8 @@ __global__ __launch_bounds__(BLK) void k_curv_conv(const Member* __restrict__ me
   __shared__ double s_p[NB], s_c[NB];
   __shared__ unsigned char s_f[NB];
   __shared__ double s_U[NS + 4][NB];
+  __shared__ double s_tab[16][6];   // TENO6 coefficients of every cut-off pattern
+  teno6_table(threadIdx.x, s_tab);
   const Member& G = mem[0];
   const long long N = G.N;
   // axes: d (faces), o (companion), r (plane)
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(BLK) void k_curv_conv(const Member* __restrict__ me
           hp[m] = fma(alpha, Uv[m], f[m]);
           hmr[5 - m] = fma(-alpha, Uv[m], f[m]);
         }
-        res = weno ? weno3z_h(hp) + weno3z_h(hmr) : teno6_h(hp, CT) + teno6_h(hmr, CT);
+        res = weno ? weno3z_h(hp) + weno3z_h(hmr) : teno6_face(s_tab, hp, hmr, CT);
       }
       out[v * N + qf] = res;
     }

@@ -206,7 +206,8 @@ __device__ __forceinline__ int wrapi(int i, int n) {
 // three 4-wave blocks per CU at its register count.
 constexpr int DTILE = 192;
 constexpr int BLKF = 256;
-constexpr int XBOX_MAX = 2208;   // convective cross staging: the three direction boxes (22*4*4 + 16*10*4 + 16*4*10)
+constexpr int XBOX_MAX = 1632;   // convective cross staging: the three direction boxes (22*4*4 + 16*10*4 + 16*4*10),
+                                 // 3 * 256 cells and the halo
 constexpr int XARM_MAX = 864;    // its halo cells: 6 per line along every axis
 constexpr int XFACE_MAX = 912;   // faces over all axes (17*4*4 + 16*5*4 + 16*4*5)
 constexpr int EXTA = 896;        // convective adjoint: tile extended by 5 + 5 along one axis

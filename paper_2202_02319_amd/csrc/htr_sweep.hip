@@ -151,20 +151,21 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
     if (tcls[bl] == 0) return;   // the lean variant has done this tile
   }
   // one spare slot past every box: a write target for threads without a halo cell
-  __shared__ double s_U[XBOX_MAX + 1], s_Fn[XBOX_MAX + 1], s_F[2][XFACE_MAX];
-  __shared__ double s_al[XFACE_MAX];   // LF speed of the TENO faces, in list order
-  // the tile's TENO faces: stencil start slot (bits 0-11), face index
-  // (12-21) and stencil stride in its box (22-31)
-  __shared__ unsigned s_tl[XFACE_MAX];
+  __shared__ double s_U[LEAN ? 1 : XBOX_MAX + 1], s_Fn[XBOX_MAX + 1], s_F[XFACE_MAX];
+  __shared__ double s_al[LEAN ? 1 : XFACE_MAX];   // LF speed of the TENO faces, in list order
+  // the tile's faces, those with TENO first and the central ones from the
+  // end: stencil start slot (bits 0-11), face index (12-21) and stencil
+  // stride in its box (22-31)
+  __shared__ unsigned s_tl[LEAN ? 1 : XFACE_MAX];
   __shared__ int s_tq[TAPE ? XFACE_MAX : 1];             // taped: the face's tape index (upper cell)
   __shared__ unsigned char s_td[TAPE ? XFACE_MAX : 1];   // taped: the face's axis
-  __shared__ int s_nt;
-  __shared__ double s_w[16][4];        // TENO6 normalised weights of every cut-off pattern
+  __shared__ int s_nt, s_nc;
+  __shared__ double s_tab[LEAN ? 1 : 16][6];   // TENO6 coefficients of every cut-off pattern
   // before the variable loop the same memory holds the LF node speed, the
   // pressure and the sensor flags
   double* s_spd = s_U;
   double* s_p = s_Fn;
-  unsigned char* s_fl = reinterpret_cast<unsigned char*>(&s_F[0][0]);
+  unsigned char* s_fl = reinterpret_cast<unsigned char*>(&s_F[0]);
   const int m = find_member_tiled(mem, nmem, bl);
   const Member& G = mem[m];
   const int t = threadIdx.x;
@@ -289,10 +290,8 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
     }
     (void)cc;
   }
-  if (t == 0) s_nt = 0;
-  if constexpr (!LEAN) {
-    if (t < 16) teno6_weights(t, s_w[t]);
-  }
+  if (t == 0) s_nt = s_nc = 0;
+  if constexpr (!LEAN) teno6_table(t, s_tab);
   __syncthreads();
   // face f of the list: axis, stencil start slot (stencil positions j-3..j+2
   // of the tile = box positions j..j+5 along d), stride along the axis, and
@@ -310,22 +309,28 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
   };
   // a stride is at most T[0] T[1] <= BLK cells
   static_assert(XBOX_MAX < (1 << 12) && XFACE_MAX < (1 << 10) && BLK < (1 << 10), "TENO list packing");
-  // this thread's faces: stencil start slot, stride, hybrid decision; TENO
-  // faces are also listed (with their Lax-Friedrichs speed) so that each
-  // variable's TENO work is spread evenly over the block
-  int fe0[XFPT], fst[XFPT];
-  unsigned fte = 0;
+  // this thread's faces: stencil start slot, stride, hybrid decision.  The
+  // full variant lists every face (the TENO ones with their Lax-Friedrichs
+  // speed), so that each variable's work is spread evenly over the block: a
+  // wave takes whole runs of 64 faces of one kind, where a thread's own
+  // central faces would cost every wave all four of its slots.  The lean
+  // variant keeps its faces in registers.
+  int fe0[LEAN ? XFPT : 1], fst[LEAN ? XFPT : 1];
   const unsigned flags = A.flags;
 #pragma unroll
   for (int k = 0; k < XFPT; ++k) {
     const int f = t + k * BLK;
-    fe0[k] = -1;
-    fst[k] = 1;
+    if constexpr (LEAN) {
+      fe0[k] = -1;
+      fst[k] = 1;
+    }
     if (f < Ftot) {
       int d, e0, bs, fb[3];
       face(f, d, e0, bs, fb);
-      fe0[k] = e0;
-      fst[k] = bs;
+      if constexpr (LEAN) {
+        fe0[k] = e0;
+        fst[k] = bs;
+      }
       bool te;
       if (flags & HTR_FORCE_TENO) te = true;
       else if (flags & HTR_FORCE_CENTRAL) te = false;
@@ -337,22 +342,26 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
         const double psi = fabs(pb - pa) / fmin(pa, pb);
         te = any != 0 || psi > psi_c;
       }
-      if (LEAN && te) {
-        atomicOr(&s_nt, 1);
-      } else if (te) {
-        fte |= 1u << k;
-        double al = s_spd[e0];
+      if constexpr (LEAN) {
+        if (te) atomicOr(&s_nt, 1);
+      } else {
+        const unsigned pk = (unsigned)e0 | (unsigned)f << 12 | (unsigned)bs << 22;
+        if (te) {
+          double al = s_spd[e0];
 #pragma unroll
-        for (int mm = 1; mm < 6; ++mm) al = fmax(al, s_spd[e0 + mm * bs]);
-        const int slot = atomicAdd(&s_nt, 1);
-        s_al[slot] = al;
-        s_tl[slot] = (unsigned)e0 | (unsigned)f << 12 | (unsigned)bs << 22;
-        if (TAPE) {
-          int g[3];
+          for (int mm = 1; mm < 6; ++mm) al = fmax(al, s_spd[e0 + mm * bs]);
+          const int slot = atomicAdd(&s_nt, 1);
+          s_al[slot] = al;
+          s_tl[slot] = pk;
+          if (TAPE) {
+            int g[3];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) g[c] = wrapi(o[c] + fb[c], G.n[c]);
-          s_tq[slot] = (int)lin(G, g);
-          s_td[slot] = (unsigned char)d;
+            for (int c = 0; c < 3; ++c) g[c] = wrapi(o[c] + fb[c], G.n[c]);
+            s_tq[slot] = (int)lin(G, g);
+            s_td[slot] = (unsigned char)d;
+          }
+        } else {
+          s_tl[Ftot - 1 - atomicAdd(&s_nc, 1)] = pk;
         }
       }
     }
@@ -404,47 +413,50 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
       nsrc = (valid && sv >= 0) ? src[sv * N + q] : 0.0;
     }
     __syncthreads();
-    double* sF = s_F[v & 1];
-    // central faces: this thread's own
-#pragma unroll
-    for (int k = 0; k < XFPT; ++k) {
-      if (fe0[k] < 0 || ((fte >> k) & 1u)) continue;
-      const int e0 = fe0[k], bs = fst[k];
+    // one face buffer: every thread has taken its differences of the last
+    // variable before the barrier above
+    double* sF = s_F;
+    // a face value goes through LDS before it is differenced, so its last
+    // rounding cannot be fused into the difference
+    auto central = [&](int e0, int bs) {
       double f6[6];
 #pragma unroll
       for (int mm = 0; mm < 6; ++mm) f6[mm] = s_Fn[e0 + mm * bs];
-      // the face value goes through LDS before it is differenced, so its
-      // last rounding cannot be fused into the difference
-      sF[t + k * BLK] =
-          (f6[0] - 8.0 * f6[1] + 37.0 * f6[2] + 37.0 * f6[3] - 8.0 * f6[4] + f6[5]) * (1.0 / 60.0);
-    }
-    // TENO faces: the tile's list, dealt round-robin over the block
-    for (int i = t; i < (LEAN ? 0 : nteno); i += BLK) {
-      const unsigned pk = s_tl[i];
-      const int e0 = pk & 0xfffu, f = (pk >> 12) & 0x3ffu, bs = pk >> 22;
-      const double al = s_al[i];
-      // the two sides of the split, without their factor 1/2
-      double hp[6], hm[6];
+      return (f6[0] - 8.0 * f6[1] + 37.0 * f6[2] + 37.0 * f6[3] - 8.0 * f6[4] + f6[5]) * (1.0 / 60.0);
+    };
+    if constexpr (LEAN) {
 #pragma unroll
-      for (int mm = 0; mm < 6; ++mm) {
-        const double f6 = s_Fn[e0 + mm * bs], u6 = s_U[e0 + mm * bs];
-        hp[mm] = fma(al, u6, f6);
-        hm[5 - mm] = fma(-al, u6, f6);
-      }
-      if (flags & HTR_WENO3Z) {
-        sF[f] = weno3z_h(hp) + weno3z_h(hm);
-        continue;
-      }
-      double qp[4], qm[4];
-      const unsigned pp = teno6_decide(hp, CT, qp), pm = teno6_decide(hm, CT, qm);
-      const double* wp = s_w[pp];
-      const double* wm = s_w[pm];
-      sF[f] = (wp[0] * qp[0] + wp[1] * qp[1] + wp[2] * qp[2] + wp[3] * qp[3]) +
-              (wm[0] * qm[0] + wm[1] * qm[1] + wm[2] * qm[2] + wm[3] * qm[3]);
-      if (TAPE) {
-        // the cut-off pattern: bits 0-3 the + side's kept candidates, 4-7 the - side's
-        const unsigned pat = pp | pm << 4;
-        bits[(long long)(s_td[i] * NV + v) * N + s_tq[i]] = (unsigned char)pat;
+      for (int k = 0; k < XFPT; ++k)
+        if (fe0[k] >= 0) sF[t + k * BLK] = central(fe0[k], fst[k]);
+    } else {
+      // the tile's list, dealt round-robin over the block
+      for (int i = t; i < Ftot; i += BLK) {
+        const unsigned pk = s_tl[i];
+        const int e0 = pk & 0xfffu, f = (pk >> 12) & 0x3ffu, bs = pk >> 22;
+        if (i >= nteno) {
+          sF[f] = central(e0, bs);
+          continue;
+        }
+        const double al = s_al[i];
+        // the two sides of the split, without their factor 1/2
+        double hp[6], hm[6];
+#pragma unroll
+        for (int mm = 0; mm < 6; ++mm) {
+          const double f6 = s_Fn[e0 + mm * bs], u6 = s_U[e0 + mm * bs];
+          hp[mm] = fma(al, u6, f6);
+          hm[5 - mm] = fma(-al, u6, f6);
+        }
+        if (flags & HTR_WENO3Z) {
+          sF[f] = weno3z_h(hp) + weno3z_h(hm);
+          continue;
+        }
+        const unsigned pp = teno6_decide(hp, CT), pm = teno6_decide(hm, CT);
+        sF[f] = teno6_value(s_tab, pp, hp) + teno6_value(s_tab, pm, hm);
+        if (TAPE) {
+          // the cut-off pattern: bits 0-3 the + side's kept candidates, 4-7 the - side's
+          const unsigned pat = pp | pm << 4;
+          bits[(long long)(s_td[i] * NV + v) * N + s_tq[i]] = (unsigned char)pat;
+        }
       }
     }
     __syncthreads();
@@ -458,11 +470,17 @@ __device__ __forceinline__ void conv_tile(int bl, const Member* __restrict__ mem
   }
 }
 
+// Bound by FP64 instructions where TENO faces are many (77% of the faces of the
+// 256x128x128 mixing layer): with the expanded indicators, four candidates
+// per side, central faces in each thread's own slots and two blocks per CU
+// (64 KB of LDS, 183 registers) a launch took 2834 us; with the shared
+// differences, one coefficient row per pattern, one list of faces and three
+// blocks per CU (48 KB, 150 registers) 1857 us.
 // MODE 0: one block per tile; 1: persistent blocks striding over the nlog
 // tiles; 2: one block per tile, also writing the TENO cut-off patterns;
 // 3: one block per tile, the tiles that k_conv_lean marked in tcls.
 template <int NS, int MODE>
-__global__ __launch_bounds__(BLK, 2) void k_conv(const MechTables* __restrict__ M, const Member* __restrict__ mem,
+__global__ __launch_bounds__(BLK, 3) void k_conv(const MechTables* __restrict__ M, const Member* __restrict__ mem,
                                               int nmem, int nlog, CallArgs A, const double* __restrict__ Ub,
                                               const double* __restrict__ auxb, const double* __restrict__ srcb,
                                               const unsigned char* __restrict__ flagb, double* __restrict__ partb,
@@ -748,7 +766,7 @@ __device__ __forceinline__ double cpR_b(const MechTables* __restrict__ M, int s,
 template <int NS>
 __device__ __forceinline__ void bnd_conv_face(const Member& G, int d, const int c[3], const double* __restrict__ U,
                                               const double* __restrict__ aux, const unsigned char* __restrict__ flag,
-                                              unsigned flags, double psi_c, double CT, double* out) {
+                                              unsigned flags, double psi_c, double CT, const double (*tab)[6], double* out) {
   constexpr int NV = NS + 4;
   const long long N = G.N;
   const int i = c[d], n = G.n[d];
@@ -802,7 +820,7 @@ __device__ __forceinline__ void bnd_conv_face(const Member& G, int d, const int 
         hp[k] = fma(al, u6[k], f6[k]);
         hm[5 - k] = fma(-al, u6[k], f6[k]);
       }
-      f = (flags & HTR_WENO3Z) ? weno3z_h(hp) + weno3z_h(hm) : teno6_h(hp, CT) + teno6_h(hm, CT);
+      f = (flags & HTR_WENO3Z) ? weno3z_h(hp) + weno3z_h(hm) : teno6_face(tab, hp, hm, CT);
     } else {
       f = 0.5 * (f6[2] + f6[3]) - 0.5 * al * (u6[3] - u6[2]);
     }
@@ -873,6 +891,9 @@ __global__ __launch_bounds__(6 * BNDC, 3) void k_bnd(const MechTables* __restric
                                                   double psi_c, double CT) {
   constexpr int NV = NS + 4, VPT = (NV + 5) / 6;
   __shared__ double s_f[6][NV][BNDC], s_acc[NV][BNDC];
+  __shared__ double s_tab[16][6];   // TENO6 coefficients of every cut-off pattern
+  teno6_table(threadIdx.x, s_tab);
+  __syncthreads();
   const Member& G = mem[0];
   const long long N = G.N;
   const int lane = threadIdx.x % BNDC, role = __builtin_amdgcn_readfirstlane(threadIdx.x / BNDC);
@@ -896,7 +917,7 @@ __global__ __launch_bounds__(6 * BNDC, 3) void k_bnd(const MechTables* __restric
   }
   const bool on_edge = a == 0 ? edge[0] : (a == 1 ? edge[1] : edge[2]);
   const bool inner = valid && G.act[a] && !on_edge;
-  if (inner) bnd_conv_face<NS>(G, a, cf, U, aux, flag, flags, psi_c, CT, &s_f[role][0][lane]);
+  if (inner) bnd_conv_face<NS>(G, a, cf, U, aux, flag, flags, psi_c, CT, s_tab, &s_f[role][0][lane]);
   __syncthreads();
   // variables role, role + 6, ...: the convective differences
   double cd[3][VPT];
