@@ -27,6 +27,7 @@ Ctx htr::bview(const htr_batch* b) {
   v.grid = b->grid;
   v.conv_split = b->conv_split;
   v.om_tab = b->ctx->om_tab;
+  for (const Member& M : b->host) v.diff_kinds |= diff_kind(M);
   v.scheme = b->ctx->scheme;
   v.total_cells = b->Ntot;
   v.timer = const_cast<Timer*>(&b->timer);

@@ -409,7 +409,7 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
   }
   {
     TimedLaunch tl(C.timer, TC_DIFF, s);
-    HIP_OK(launch_diff(C.ns, C.M, C.mem, C.nmem, C.ndtblocks, C.grid, a, U, Un, T, w.aux, w.grad, w.part, out, ca,
+    HIP_OK(launch_diff(C.ns, C.M, C.mem, C.nmem, C.ndtblocks, C.grid, C.diff_kinds, a, U, Un, T, w.aux, w.grad, w.part, out, ca,
                        cb,
                        rhs_only, s));
   }
@@ -468,6 +468,7 @@ Ctx htr::view(const htr_ctx* c) {
   v.grid = c->grid;
   v.conv_split = c->conv_split;
   v.om_tab = c->om_tab;
+  v.diff_kinds = diff_kind(c->host_mem);
   v.scheme = c->scheme;
   v.total_cells = c->N;
   for (int a = 0; a < 3; ++a) {

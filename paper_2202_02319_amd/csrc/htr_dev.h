@@ -87,7 +87,7 @@ struct Member {
   int ntile[3];               // tiles per axis
   int tblock_begin;           // first block of this member in tiled launches
   int ntblocks;
-  int dtdim[3];               // tile of the diffusive sweep (DTILE cells)
+  int dtdim[3];               // tile of the diffusive sweep
   int dntile[3];
   int dtblock_begin;          // first block of this member in diffusive-sweep launches
   int ndtblocks;
@@ -201,11 +201,14 @@ __device__ __forceinline__ int wrapi(int i, int n) {
 
 // Staging limits of the tiled kernels; a tile shape is accepted only if it
 // fits all of them (tile_shape_ok).
-// The diffusive sweep: DTILE-cell tiles in blocks of BLKF threads, one face
-// per thread along each axis (a tile has at most BLKF faces along any axis):
-// three 4-wave blocks per CU at its register count.
+// The diffusive sweep: tiles of BLK cells and at most BLK halo nodes, BLK
+// lower faces along an axis and at most 64 upper ones of its last layer.
+constexpr int DNODE = 2 * BLK;
+// Its variant for grids of fewer axes: DTILE-cell tiles in blocks of BLKF
+// threads, one face per thread along each axis.
 constexpr int DTILE = 192;
 constexpr int BLKF = 256;
+constexpr int DFACE = BLK + 64;
 constexpr int XBOX_MAX = 1632;   // convective cross staging: the three direction boxes (22*4*4 + 16*10*4 + 16*4*10),
                                  // 3 * 256 cells and the halo
 constexpr int XARM_MAX = 864;    // its halo cells: 6 per line along every axis
@@ -252,7 +255,10 @@ hipError_t launch_conv(int ns, const MechTables* M, const Member* mem, int nmem,
 hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, const Member& host, const CallArgs& a, const double* U,
                       const double* T, const double* aux, const double* src, const unsigned char* flag,
                       const double* grad, double* part, double psi_c, double CT, hipStream_t s);
-hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid,
+// kinds: DIFF_* of the members there are.
+constexpr unsigned DIFF_FLAT = 1u, DIFF_3D = 2u;
+inline unsigned diff_kind(const Member& M) { return M.act[0] && M.act[1] && M.act[2] ? DIFF_3D : DIFF_FLAT; }
+hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid, unsigned kinds,
                        const CallArgs& a,
                        const double* U, const double* Un, const double* T, const double* aux, const double* grad,
                        const double* part, double* out, double ca, double cb, int rhs_only, hipStream_t s);

@@ -95,6 +95,7 @@ struct Ctx {
   int n1[3] = {1, 1, 1};          // grid of the single-member case (laser normalisation)
   double L1[3] = {1, 1, 1};
   Timer* timer = nullptr;
+  unsigned diff_kinds = 0;        // DIFF_* of the members
   bool bounded = false;           // single grid with non-periodic boundaries (boundary kernel)
   // curvilinear single grid (null: rectilinear sweeps)
   const CurvGeom* curv = nullptr;

@@ -11,10 +11,12 @@
 // Two tiled kernels per stage: k_conv (sources and convective flux
 // differences, one block per 256-cell tile with the tile and its halo staged
 // in LDS) and k_diff (diffusive flux differences and the stage update, one
-// block per 192-cell tile of its own).  Every face is evaluated once, so the
+// block per 256-cell tile of its own).  Every face is evaluated once, so the
 // scheme is exactly conservative.
 
 #include <math.h>
+
+#include <type_traits>
 
 #include "htr_dev.h"
 #include "htr_flux.h"
@@ -63,22 +65,21 @@ bool tile_shape_ok(const int act[3], const int t[3], const char** why) {
   return w == nullptr;
 }
 
-// The diffusive sweep's tile for the active axes: 16 x 4 x 3 in 3-D (204,
-// 240 and 256 faces), 16 x 12 over the two active axes of 2-D grids (204 and
-// 208), 192 along a 1-D grid.
+// The diffusive sweep's tile for the active axes: 8 x 8 x 4 in 3-D (its 256
+// halo nodes are one per thread); for k_diff_flat 16 x 12 over the two active
+// axes of a 2-D grid (204 and 208 faces) and 192 along a 1-D grid.
 static void diff_tile_shape(const int act[3], int t[3]) {
   const int na = act[0] + act[1] + act[2];
-  t[0] = t[1] = t[2] = 1;
+  default_tile_shape(act, t);
   if (na == 3) {
-    t[0] = 16; t[1] = 4; t[2] = 3;
+    t[0] = 8; t[1] = 8; t[2] = 4;
   } else if (na == 2) {
     int k = 0;
     for (int a = 0; a < 3; ++a)
       if (act[a]) t[a] = k++ == 0 ? 16 : 12;
-  } else if (na == 1) {
-    for (int a = 0; a < 3; ++a) t[a] = act[a] ? DTILE : 1;
   } else {
-    t[0] = DTILE;
+    for (int a = 0; a < 3; ++a)
+      if (t[a] > 1) t[a] = DTILE;
   }
 }
 
@@ -647,13 +648,20 @@ __device__ __forceinline__ void diff_dir(const MechTables* __restrict__ M, const
   __syncthreads();
 }
 
-// Diffusive flux differences (each face once, exchanged through LDS) added
-// to part, then the SSP-RK3 stage combination (or dU/dt when rhs_only).
-// The diffusive sweep's own tiles (dtdim, DTILE cells): BLKF threads, the
-// first DTILE own the tile's cells, and every thread owns one face per
-// direction (a tile has at most BLKF faces along any axis).
+// Members with three active axes are k_diff's, the others k_diff_flat's; each
+// kernel passes over the blocks of the other's.
+__device__ __forceinline__ bool three_axes(const Member& G) { return G.act[0] && G.act[1] && G.act[2]; }
+
+// The sweep of grids with one or two active axes: diffusive flux
+// differences (each face once, exchanged through LDS) added to part, then the
+// SSP-RK3 stage combination (or dU/dt when rhs_only).  Tiles of DTILE cells in
+// BLKF threads, the first DTILE own the cells, and every thread owns one face
+// per direction (a tile has at most BLKF faces along any axis), whose nodes'
+// fields it reads itself.  With one or two directions that costs fewer loads
+// than the staged species of k_diff cost barriers: 6.0 against 10.0 us on 256
+// cells along a line (five species), 20.0 against 23.6 us on 384x250 (nine).
 template <int NS>
-__device__ __forceinline__ void diff_tile(int bl, const MechTables* __restrict__ M, const Member* __restrict__ mem,
+__device__ __forceinline__ void diff_flat_tile(int bl, const MechTables* __restrict__ M, const Member* __restrict__ mem,
                                           int nmem, const CallArgs& A, const double* __restrict__ Ub,
                                           const double* Unb, const double* __restrict__ Tb,
                                           const double* __restrict__ auxb, const double* __restrict__ gradb,
@@ -720,17 +728,410 @@ __device__ __forceinline__ void diff_tile(int bl, const MechTables* __restrict__
 }
 
 template <int NS, bool PERSIST>
-__global__ __launch_bounds__(BLKF, 3) void k_diff(const MechTables* __restrict__ M, const Member* __restrict__ mem,
+__global__ __launch_bounds__(BLKF, 3) void k_diff_flat(const MechTables* __restrict__ M, const Member* __restrict__ mem,
                                                   int nmem, int nlog, CallArgs A, const double* __restrict__ Ub,
                                                   const double* Unb, const double* __restrict__ Tb,
                                                   const double* __restrict__ auxb, const double* __restrict__ gradb,
                                                   const double* __restrict__ partb, double* outb, double ca,
                                                   double cb, int rhs_only) {
   if (!PERSIST) {
+    if (three_axes(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff's
+    diff_flat_tile<NS>(blockIdx.x, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
+    return;
+  }
+  for (int bl = blockIdx.x; bl < nlog; bl += gridDim.x) {
+    if (three_axes(mem[find_member_dtiled(mem, nmem, bl)])) continue;
+    diff_flat_tile<NS>(bl, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
+    __syncthreads();   // the next tile reuses the LDS
+  }
+}
+
+// Diffusive flux differences added to part, then the SSP-RK3 stage
+// combination (or dU/dt when rhs_only), on the diffusive sweep's own tiles
+// (dtdim, BLK cells, one per thread).
+//
+// Thread t owns cell t, its box node and one halo node, and the lower face of
+// its cell along every axis; the upper faces of the tile's last layer along
+// axis d go to the lanes of wavefront d + 1.  The nodes' fields are loaded
+// once, and what a node contributes to its faces (mole and mass fraction,
+// enthalpy, 1/rho) is formed once and passed through LDS one species at a
+// time, so no per-variable array is held: the species' correction flux
+// first, then each species' flux, whose differences finish that row.
+// Every value that two faces or cells difference has been through LDS, so its
+// last rounding cannot be fused into the difference.
+//
+// Bound by the rate at which the address and data units of L1 take its loads
+// (the data unit is busy 84% of the time).  One face per thread reading both of
+// its nodes' thirty fields (about 320 loads a cell) took 592 us at 128^3 cells
+// and nine species, 1145 us at 256x128x128; this order (about 110) takes 452
+// and 876 us at two blocks per CU.  At three blocks (168 registers) 13 values
+// spill and it takes 582 us; a deeper prefetch of the rows and twice as many
+// barriers change nothing.
+template <int NS>
+__device__ __forceinline__ void diff_tile(int bl, const MechTables* __restrict__ M, const Member* __restrict__ mem,
+                                          int nmem, const CallArgs& A, const double* __restrict__ Ub,
+                                          const double* Unb, const double* __restrict__ Tb,
+                                          const double* __restrict__ auxb, const double* __restrict__ gradb,
+                                          const double* __restrict__ partb, double* outb, double ca, double cb,
+                                          int rhs_only) {
+  constexpr int NV = NS + 4, NAUX = 7 + NS;
+  // node records (cell t at slot t, halo node h at BLK + h, so that lanes of
+  // a row read consecutive banks): first thirteen of the velocity, viscosity
+  // and velocity gradient, then four of the conduction, then four each of two
+  // species; behind the first eight, per axis a value for each lower face and
+  // each upper one of the last layer, for up to three rows at once
+  __shared__ double s_mem[8 * DNODE + 9 * DFACE];
+  double (*s_n)[DNODE] = reinterpret_cast<double (*)[DNODE]>(s_mem);
+  double (*s_F)[3][DFACE] = reinterpret_cast<double (*)[3][DFACE]>(s_mem + 8 * DNODE);
+  static_assert(13 * DNODE <= 8 * DNODE + 9 * DFACE, "the gradient records fit");
+  const int m = find_member_dtiled(mem, nmem, bl);
+  const Member& G = mem[m];
+  const int t = threadIdx.x;
+  int o[3];
+  tile_origin_of(G.dtdim, G.dntile, G.ndtblocks, bl - G.dtblock_begin, o);
+  const int T[3] = {G.dtdim[0], G.dtdim[1], G.dtdim[2]};
+  const bool act[3] = {G.act[0] != 0, G.act[1] != 0, G.act[2] != 0};
+  const int l[3] = {t % T[0], (t / T[0]) % T[1], t / (T[0] * T[1])};
+  const int gc[3] = {o[0] + l[0], o[1] + l[1], o[2] + l[2]};
+  const bool valid = gc[0] < G.n[0] && gc[1] < G.n[1] && gc[2] < G.n[2];
+  const long long N = G.N;
+  const double* U = Ub + NV * G.off;
+  const double* part = partb + NV * G.off;
+  const double* Un = Unb + NV * G.off;
+  double* out = outb + NV * G.off;
+  int gw[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) gw[a] = wrapi(gc[a], G.n[a]);
+  const long long qc = lin(G, gw);
+  const double dt = rhs_only ? 0.0 : A.dt_dev[m];
+  // row v of the update; its loads come before the row's face work (out may
+  // be the array U^n, so they could not move above an earlier row's store)
+  struct Row { double p, u, un; };
+  const double* un_or_part = !rhs_only && ca != 0.0 ? Un : part;   // U^n where it enters
+  auto row = [&](int v, double u) { return Row{part[v * N + qc], u, un_or_part[v * N + qc]}; };
+  // next to a non-periodic boundary part[] holds the whole right-hand side
+  // (the boundary kernel's): no diffusive term is added there
+  const bool slab = in_boundary_slab(G, gc);
+  auto finish = [&](int v, const Row& r, double acc) {
+    if (!valid) return;
+    if (slab) acc = 0.0;
+    if (rhs_only) {
+      out[v * N + qc] = r.p + acc;
+    } else {
+      const double base = r.u + dt * (r.p + acc);
+      out[v * N + qc] = ca != 0.0 ? ca * r.un + cb * base : cb * base;
+    }
+  };
+  if (A.flags & HTR_VISC_OFF) {
+    Row r[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) r[v] = row(v, U[v * N + qc]);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) finish(v, r[v], 0.0);
+    return;
+  }
+  const double* Tf = Tb + G.off;
+  const double* aux = auxb + NAUX * G.off;
+  const double* grad = gradb + 9 * G.off;
+  // halo nodes: per axis the layer below the tile, then the one above, each
+  // by the two other axes in order; this thread's one
+  int hoff[3];
+  hoff[0] = BLK;
+  hoff[1] = hoff[0] + (act[0] ? 2 * (BLK / T[0]) : 0);
+  hoff[2] = hoff[1] + (act[1] ? 2 * (BLK / T[1]) : 0);
+  const int nhalo = hoff[2] + (act[2] ? 2 * (BLK / T[2]) : 0) - BLK;
+  const int sh = BLK + t;
+  long long qh = qc;
+  int dh = 0;   // the halo node's axis
+  if (t < nhalo) {
+    const int d = sh < hoff[1] ? 0 : (sh < hoff[2] ? 1 : 2);
+    const int Td = d == 0 ? T[0] : (d == 1 ? T[1] : T[2]), S = BLK / Td;
+    const int r = sh - (d == 0 ? hoff[0] : (d == 1 ? hoff[1] : hoff[2]));
+    const int x = r % S, w = r < S ? -1 : Td;
+    const int Te = d == 0 ? T[1] : T[0];
+    const int x0 = x % Te, x1 = x / Te;
+    const int h[3] = {d == 0 ? w : x0, d == 1 ? w : (d == 0 ? x0 : x1), d == 2 ? w : x1};
+    int g[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) g[a] = wrapi(o[a] + h[a], G.n[a]);
+    qh = lin(G, g);
+    dh = d;
+  }
+  // slot of the lower neighbour of this cell along each axis
+  const int pos[3] = {l[1] + T[1] * l[2], l[0] + T[0] * l[2], l[0] + T[0] * l[1]};
+  const int lo[3] = {l[0] > 0 ? t - 1 : hoff[0] + pos[0], l[1] > 0 ? t - T[0] : hoff[1] + pos[1],
+                     l[2] > 0 ? t - T[0] * T[1] : hoff[2] + pos[2]};
+  double rc[NS], rh[NS], Dc[NS], Dh[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    rc[s] = U[s * N + qc];
+    rh[s] = U[s * N + qh];
+  }
+  const double Tc = Tf[qc], Th = Tf[qh];
+  // this cell's record: u, v, w, mu, the nine velocity derivatives; a halo
+  // node serves the faces of its own axis only, with the six derivatives
+  // tangential to them
+  double nd[13], lamc, lamh;
+  {
+    double hd[10];
+    const int h1 = 3 * ((dh + 1) % 3), h2 = 3 * ((dh + 2) % 3);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int a = k < 3 ? 4 + k : 2;
+      nd[k] = aux[a * N + qc];
+      hd[k] = aux[a * N + qh];
+    }
+    lamc = aux[3 * N + qc];
+    lamh = aux[3 * N + qh];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) nd[4 + k] = grad[k * N + qc];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      hd[4 + k] = grad[(h1 + k) * N + qh];
+      hd[7 + k] = grad[(h2 + k) * N + qh];
+    }
+#pragma unroll
+    for (int k = 0; k < 13; ++k) s_n[k][t] = nd[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s_n[k][sh] = hd[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      s_n[4 + h1 + k][sh] = hd[4 + k];
+      s_n[4 + h2 + k][sh] = hd[7 + k];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    Dc[s] = aux[(7 + s) * N + qc];
+    Dh[s] = aux[(7 + s) * N + qh];
+  }
+  double rhoc = 0.0, rhoh = 0.0, nc = 0.0, nh = 0.0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    rhoc += rc[s];
+    rhoh += rh[s];
+    nc += rc[s] * M->iW[s];
+    nh += rh[s] * M->iW[s];
+  }
+  const double inc = 1.0 / nc, inh = 1.0 / nh, irc = 1.0 / rhoc, irh = 1.0 / rhoh;
+  // faces: 0-2 the lower face of this cell along each axis (its upper node's
+  // values in registers), 3 (wavefront d + 1) an upper face of the last layer
+  // along d, between slots sx and ux
+  const int xd = __builtin_amdgcn_readfirstlane(t >> 6) - 1, lane = t & 63;
+  const bool has_x = xd >= 0 && act[xd < 0 ? 0 : xd] && lane < BLK / T[xd < 0 ? 0 : xd];
+  int sx = 0, ux = 0;
+  double xfx = 0.0;   // metric of that face
+  if (has_x) {
+    const int Te = xd == 0 ? T[1] : T[0];
+    const int x0 = lane % Te, x1 = lane / Te;
+    const int h[3] = {xd == 0 ? T[0] - 1 : x0, xd == 1 ? T[1] - 1 : (xd == 0 ? x0 : x1), xd == 2 ? T[2] - 1 : x1};
+    xfx = G.xif[xd][wrapi(o[xd] + T[xd] - 1, G.n[xd])];
+    sx = h[0] + T[0] * (h[1] + T[1] * h[2]);
+    ux = (xd == 0 ? hoff[0] : (xd == 1 ? hoff[1] : hoff[2])) + BLK / T[xd] + lane;
+  }
+  // where the upper face of this cell along d is in s_F[.][d]
+  const int up[3] = {l[0] + 1 < T[0] ? t + 1 : BLK + pos[0], l[1] + 1 < T[1] ? t + T[0] : BLK + pos[1],
+                     l[2] + 1 < T[2] ? t + T[0] * T[1] : BLK + pos[2]};
+  double xi[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) xi[d] = act[d] ? G.xin[d][gw[d]] : 0.0;
+  // flux difference of a row: the upper faces from s_F[z], the lower ones F
+  auto difference = [&](int z, auto F) {
+    double acc = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (act[d]) acc += xi[d] * (s_F[z][d][up[d]] - F(d));
+    return acc;
+  };
+  // rounds x before it meets another value (no operation of its own)
+  auto rounded = [](double x) {
+    asm("" : "+v"(x));
+    return x;
+  };
+  double k1[4] = {}, corr[4] = {}, en[4] = {}, tau[4][3];
+  double xf[4];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) xf[d] = act[d] ? G.xif[d][gw[d] > 0 ? gw[d] - 1 : G.n[d] - 1] : 0.0;
+  xf[3] = xfx;
+  Row mrow[3], srow[NS];
+#pragma unroll
+  for (int mm = 0; mm < 3; ++mm) mrow[mm] = row(NS + mm, U[(NS + mm) * N + qc]);
+  __syncthreads();
+  // viscous stress of face k along d (lower node in slot sa, upper node's
+  // record B) and its work
+  auto viscous = [&](auto dc, int sa, auto B, int k) {
+    constexpr int d = decltype(dc)::value, t1 = (d + 1) % 3, t2 = (d + 2) % 3;
+    double g[3][3], uf[3];
+#pragma unroll
+    for (int mm = 0; mm < 3; ++mm) {
+      g[t1][mm] = 0.5 * (s_n[4 + 3 * t1 + mm][sa] + B(4 + 3 * t1 + mm));
+      g[t2][mm] = 0.5 * (s_n[4 + 3 * t2 + mm][sa] + B(4 + 3 * t2 + mm));
+      const double uA = s_n[mm][sa], uB = B(mm);
+      g[d][mm] = xf[k] * (uB - uA);
+      uf[mm] = 0.5 * (uA + uB);
+    }
+    const double muf = 0.5 * (s_n[3][sa] + B(3));
+    const double divu = g[0][0] + g[1][1] + g[2][2];
+    double work = 0.0;
+#pragma unroll
+    for (int mm = 0; mm < 3; ++mm) {
+      double tm = muf * (g[d][mm] + g[mm][d]);
+      if (mm == d) tm -= (2.0 / 3.0) * muf * divu;
+      tau[k][mm] = rounded(tm);
+      work += tau[k][mm] * uf[mm];
+    }
+    en[k] = work;
+  };
+  constexpr std::integral_constant<int, 0> d0{};
+  constexpr std::integral_constant<int, 1> d1{};
+  constexpr std::integral_constant<int, 2> d2{};
+  auto own = [&](int k) { return nd[k]; };
+  auto above = [&](int k) { return s_n[k][ux]; };
+  if (act[0]) viscous(d0, lo[0], own, 0);
+  if (act[1]) viscous(d1, lo[1], own, 1);
+  if (act[2]) viscous(d2, lo[2], own, 2);
+  if (has_x) {
+    if (xd == 0) viscous(d0, sx, above, 3);
+    else if (xd == 1) viscous(d1, sx, above, 3);
+    else viscous(d2, sx, above, 3);
+  }
+  __syncthreads();
+  // conduction and the species' face factor rho xf / W
+  {
+    const double c[4] = {lamc, Tc, rhoc, rhoc * inc}, h[4] = {lamh, Th, rhoh, rhoh * inh};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s_n[k][t] = c[k];
+      s_n[k][sh] = h[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k < 3 ? !act[k] : !has_x) continue;
+      const int a = k < 3 ? lo[k] : sx;
+      double B[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) B[j] = k < 3 ? c[j] : s_n[j][ux];
+      en[k] += 0.5 * (s_n[0][a] + B[0]) * xf[k] * (B[1] - s_n[1][a]);
+      k1[k] = 0.5 * (s_n[2][a] + B[2]) * xf[k] / (0.5 * (s_n[3][a] + B[3]));
+    }
+  }
+  // the first species' rows
+#pragma unroll
+  for (int s = 0; s < 2 && s < NS; ++s) srow[s] = row(s, rc[s]);
+  // every face's value of one row into s_F[z]
+  auto put = [&](int z, auto val) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (act[d]) s_F[z][d][t] = val(d);
+    if (has_x) s_F[z][xd][BLK + lane] = val(3);
+  };
+#pragma unroll
+  for (int mm = 0; mm < 3; ++mm) put(mm, [&](int k) { return tau[k][mm]; });
+  __syncthreads();
+#pragma unroll
+  for (int mm = 0; mm < 3; ++mm) finish(NS + mm, mrow[mm], difference(mm, [&](int d) { return tau[d][mm]; }));
+  // species in twos: the correction flux first, the records in alternating halves
+#pragma unroll
+  for (int s0 = 0; s0 < NS; s0 += 2) {
+    double (*R)[DNODE] = &s_n[(4 + 2 * s0) % 8];
+    double X[2];
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+      const int s = s0 + j;
+      X[j] = rounded(rc[s] * M->iW[s] * inc);
+      R[2 * j][t] = X[j];
+      R[2 * j][sh] = rh[s] * M->iW[s] * inh;
+      R[2 * j + 1][t] = Dc[s];
+      R[2 * j + 1][sh] = Dh[s];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k < 3 ? !act[k] : !has_x) continue;
+      const int a = k < 3 ? lo[k] : sx;
+#pragma unroll
+      for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+        const double Xb = k < 3 ? X[j] : R[2 * j][ux], Db = k < 3 ? Dc[s0 + j] : R[2 * j + 1][ux];
+        corr[k] += k1[k] * (0.5 * M->W[s0 + j] * (R[2 * j + 1][a] + Db)) * (Xb - R[2 * j][a]);
+      }
+    }
+  }
+  __syncthreads();
+  // each species' flux and its enthalpy; the energy row goes with the last ones
+  const double iTc = 1.0 / Tc, iTh = 1.0 / Th;
+  Row er{};
+#pragma unroll
+  for (int s0 = 0; s0 < NS; s0 += 2) {
+    const bool last = s0 + 2 >= NS;
+    // the next rows' loads, ahead of this group's stores: a wavefront's
+    // memory operations complete in order
+#pragma unroll
+    for (int j = 2; j < 4; ++j)
+      if (s0 + j < NS) srow[s0 + j] = row(s0 + j, rc[s0 + j]);
+    if (last) er = row(NS + 3, U[(NS + 3) * N + qc]);
+    double X[2], Y[2], H[2];
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+      const int s = s0 + j;
+      X[j] = rounded(rc[s] * M->iW[s] * inc);
+      Y[j] = rounded(rc[s] * irc);
+      H[j] = rounded(M->RW[s] * Tc * hRTi(M, s, Tc, iTc));
+      s_n[4 * j][t] = X[j];
+      s_n[4 * j][sh] = rh[s] * M->iW[s] * inh;
+      s_n[4 * j + 1][t] = Dc[s];
+      s_n[4 * j + 1][sh] = Dh[s];
+      s_n[4 * j + 2][t] = Y[j];
+      s_n[4 * j + 2][sh] = rh[s] * irh;
+      s_n[4 * j + 3][t] = H[j];
+      s_n[4 * j + 3][sh] = M->RW[s] * Th * hRTi(M, s, Th, iTh);
+    }
+    __syncthreads();
+    double F[2][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      F[0][k] = F[1][k] = 0.0;
+      if (k < 3 ? !act[k] : !has_x) continue;
+      const int a = k < 3 ? lo[k] : sx;
+#pragma unroll
+      for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+        const double (*R)[DNODE] = &s_n[4 * j];
+        const double Xb = k < 3 ? X[j] : R[0][ux], Db = k < 3 ? Dc[s0 + j] : R[1][ux];
+        const double Yb = k < 3 ? Y[j] : R[2][ux], Hb = k < 3 ? H[j] : R[3][ux];
+        F[j][k] = rounded(k1[k] * (0.5 * M->W[s0 + j] * (R[1][a] + Db)) * (Xb - R[0][a]) -
+                          0.5 * (R[2][a] + Yb) * corr[k]);
+        en[k] += F[j][k] * (0.5 * (R[3][a] + Hb));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) put(j, [&](int k) { return F[j][k]; });
+    if (last) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) en[k] = rounded(en[k]);
+      put(2, [&](int k) { return en[k]; });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j)
+      finish(s0 + j, srow[s0 + j], difference(j, [&](int d) { return F[j][d]; }));
+    if (last) finish(NS + 3, er, difference(2, [&](int d) { return en[d]; }));
+  }
+}
+
+template <int NS, bool PERSIST>
+__global__ __launch_bounds__(BLK, 2) void k_diff(const MechTables* __restrict__ M, const Member* __restrict__ mem,
+                                                 int nmem, int nlog, CallArgs A, const double* __restrict__ Ub,
+                                                 const double* Unb, const double* __restrict__ Tb,
+                                                 const double* __restrict__ auxb, const double* __restrict__ gradb,
+                                                 const double* __restrict__ partb, double* outb, double ca,
+                                                 double cb, int rhs_only) {
+  if (!PERSIST) {
+    if (!three_axes(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff_flat's
     diff_tile<NS>(blockIdx.x, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     return;
   }
   for (int bl = blockIdx.x; bl < nlog; bl += gridDim.x) {
+    if (!three_axes(mem[find_member_dtiled(mem, nmem, bl)])) continue;
     diff_tile<NS>(bl, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     __syncthreads();   // the next tile reuses the LDS
   }
@@ -1110,15 +1511,22 @@ static hipError_t conv_t(const MechTables* M, const Member* mem, int nmem, int n
 }
 
 template <int NS>
-static hipError_t diff_t(const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid, const CallArgs& a,
+static hipError_t diff_t(const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid, unsigned kinds,
+                         const CallArgs& a,
                          const double* U, const double* Un, const double* T, const double* aux, const double* grad,
                          const double* part, double* out, double ca, double cb, int rhs_only, hipStream_t s) {
-  if (grid < ntblocks)
-    hipLaunchKernelGGL((k_diff<NS, true>), dim3(grid), dim3(BLKF), 0, s, M, mem, nmem, ntblocks, a, U, Un, T, aux,
-                       grad, part, out, ca, cb, rhs_only);
-  else
-    hipLaunchKernelGGL((k_diff<NS, false>), dim3(grid), dim3(BLKF), 0, s, M, mem, nmem, ntblocks, a, U, Un, T, aux,
-                       grad, part, out, ca, cb, rhs_only);
+#define D_(KERNEL, PERSIST, GRID, THREADS)                                                                            \
+  hipLaunchKernelGGL((KERNEL<NS, PERSIST>), dim3(GRID), dim3(THREADS), 0, s, M, mem, nmem, ntblocks, a, U, Un, T, aux, \
+                     grad, part, out, ca, cb, rhs_only)
+  if (kinds & DIFF_FLAT) {
+    if (grid < ntblocks) D_(k_diff_flat, true, grid, BLKF);
+    else D_(k_diff_flat, false, ntblocks, BLKF);
+  }
+  if (kinds & DIFF_3D) {
+    if (grid < ntblocks) D_(k_diff, true, grid, BLK);
+    else D_(k_diff, false, ntblocks, BLK);
+  }
+#undef D_
   return hipGetLastError();
 }
 
@@ -1132,12 +1540,12 @@ hipError_t launch_conv(int ns, const MechTables* M, const Member* mem, int nmem,
 #undef C_
 }
 
-hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid,
+hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid, unsigned kinds,
                        const CallArgs& a, const double* U, const double* Un, const double* T, const double* aux,
                        const double* grad, const double* part, double* out, double ca, double cb, int rhs_only,
                        hipStream_t s) {
   grid = grid_of(ntblocks, grid);
-#define C_(NS) diff_t<NS>(M, mem, nmem, ntblocks, grid, a, U, Un, T, aux, grad, part, out, ca, cb, rhs_only, s)
+#define C_(NS) diff_t<NS>(M, mem, nmem, ntblocks, grid, kinds, a, U, Un, T, aux, grad, part, out, ca, cb, rhs_only, s)
   HTR_NS_SWITCH(ns, C_);
 #undef C_
 }
