@@ -355,7 +355,7 @@ TimedLaunch::~TimedLaunch() {
 // want_dt: the per-cell kernel also reduces the stable step and writes dt_dev.
 htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const double* U, const double* Un,
                  double* T, double* out, double ca, double cb, int rhs_only, double* hrr, double* J_dev,
-                 double jcoef, hipStream_t s, int want_dt, double* dt_out, unsigned char* teno_bits) {
+                 double jcoef, hipStream_t s, int want_dt, double* dt_out, unsigned char* teno_bits, double* t_adv) {
   const bool need_red = J_dev != nullptr || want_dt;
   {
     TimedLaunch tl(C.timer, TC_POINT, s);
@@ -364,7 +364,7 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
   }
   if (need_red) {
     TimedLaunch tl(C.timer, TC_REDUCE, s);
-    HIP_OK(launch_finalize(C.mem, C.nmem, w.blkred, C.scheme.cfl, dt_out, J_dev, a.dt_dev, jcoef, want_dt, s));
+    HIP_OK(launch_finalize(C.mem, C.nmem, w.blkred, C.scheme.cfl, dt_out, J_dev, a.dt_dev, jcoef, want_dt, t_adv, s));
   }
   if (C.curv) {
     // curvilinear grid: mapped fluxes through per-face kernels, then the update
@@ -440,7 +440,7 @@ htr_status rk3(const Ctx& C, const Workspace& w, double* U, double* T, double* t
     TapeView tv{};
     if (tape) tv = tape_view(tape, C.ns, tot, k);
     htr_status st = stage(C, w, a, in[k], U, T, out[k], ca[k], cb[k], 0, nullptr, J_dev, bq[k], s,
-                          k == 0 && compute_dt, dt_dev, tape ? tv.bits : nullptr);
+                          k == 0 && compute_dt, dt_dev, tape ? tv.bits : nullptr, k == 2 && J_dev ? t_dev : nullptr);
     if (st) return st;
     if (tape) {
       // the stage's per-cell fields, temperature and sensor flags, as its sweeps used them
@@ -449,8 +449,10 @@ htr_status rk3(const Ctx& C, const Workspace& w, double* U, double* T, double* t
       HIP_OK(hipMemcpyAsync(tv.flag, w.flag, tot, hipMemcpyDeviceToDevice, s));
     }
   }
-  TimedLaunch tl(C.timer, TC_REDUCE, s);
-  HIP_OK(launch_advance_time(C.nmem, t_dev, dt_dev, s));
+  if (!J_dev) {   // with J, the last stage's reduction has advanced the time
+    TimedLaunch tl(C.timer, TC_REDUCE, s);
+    HIP_OK(launch_advance_time(C.nmem, t_dev, dt_dev, s));
+  }
   return HTR_OK;
 }
 
@@ -804,7 +806,7 @@ htr_status htr_stable_dt(htr_ctx* c, const double* U, double* T_io, double* dt_d
   hipStream_t s = (hipStream_t)stream;
   HIP_OK(launch_point(C.ns, C.M, C.mem, 1, C.nblocks, 0, a, U, T_io, c->ws.aux, c->ws.src, nullptr, c->ws.blkred,
                       nullptr, c->ws.status, 1, C.om_tab, s, C.curv));
-  HIP_OK(launch_finalize(C.mem, 1, c->ws.blkred, c->scheme.cfl, dt_dev, nullptr, nullptr, 0.0, 1, s));
+  HIP_OK(launch_finalize(C.mem, 1, c->ws.blkred, c->scheme.cfl, dt_dev, nullptr, nullptr, 0.0, 1, nullptr, s));
   return HTR_OK;
 }
 

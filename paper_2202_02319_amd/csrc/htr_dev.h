@@ -271,8 +271,10 @@ void set_tiles(Member& M, const int* shape, int* tblocks, int* dtblocks);
 bool tile_shape_ok(const int act[3], const int shape[3], const char** why);
 // Default tile shape for the active axes.
 void default_tile_shape(const int act[3], int shape[3]);
+// t_adv (nullable): per-member time to advance by the step.
 hipError_t launch_finalize(const Member* mem, int nmem, const double* blkred, double cfl, double* dt_dev,
-                           double* J_dev, const double* dt_in, double jcoef, int want_dt, hipStream_t s);
+                           double* J_dev, const double* dt_in, double jcoef, int want_dt, double* t_adv,
+                           hipStream_t s);
 hipError_t launch_advance_time(int nmem, double* t_dev, const double* dt_dev, hipStream_t s);
 hipError_t launch_member_max(const Member* mem, int nmem, const double* field, double* out, int accumulate,
                              hipStream_t s);

@@ -113,7 +113,8 @@ htr_status ws_alloc(Workspace& w, int ns, long long N, int nblocks, int nmem);
 void ws_free(Workspace& w);
 htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const double* U, const double* Un, double* T,
                  double* out, double ca, double cb, int rhs_only, double* hrr, double* J_dev, double jcoef,
-                 hipStream_t s, int want_dt, double* dt_out, unsigned char* teno_bits = nullptr);
+                 hipStream_t s, int want_dt, double* dt_out, unsigned char* teno_bits = nullptr,
+                 double* t_adv = nullptr);
 // Looks up, once per device and with that device current, the device
 // address of the no-allocation step's scratch array (htr_noalloc.hip).
 htr_status noalloc_init(int device);
