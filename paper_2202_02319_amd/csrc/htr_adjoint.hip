@@ -31,6 +31,7 @@
 
 #include "htr_dev.h"
 #include "htr_flux.h"
+#include "htr_math.h"
 
 namespace htr {
 
@@ -131,8 +132,11 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
     nB += b * M->iW[k];
   }
   const double rhof = 0.5 * (rA + rB);
-  const double Wf = 0.5 * (rA / nA + rB / nB);
-  const double TA = T[qA], TB = T[qB];
+  // reciprocals once per face: the species passes divide by them throughout
+  // (340 us a launch at 64^3 cells with the quotients, 281 without)
+  const double inA = 1.0 / nA, inB = 1.0 / nB, irA = 1.0 / rA, irB = 1.0 / rB;
+  const double Wf = 0.5 * (rA * inA + rB * inB), iWf = 1.0 / Wf;
+  const double TA = T[qA], TB = T[qB], iTA = 1.0 / TA, iTB = 1.0 / TB;
   // pass 1: corr = sum_k term_k (per-species values are recomputed from
   // cached loads in every pass instead of being held in registers)
   double corr = 0.0;
@@ -140,8 +144,8 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] / nB - a * M->iW[k] / nA);
-    corr += rhof * Df * (M->W[k] / Wf) * dX;
+    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    corr += rhof * Df * (M->W[k] * iWf) * dX;
   }
   // ---- reverse
   const double qnb = -Gv[NS + 3];
@@ -157,11 +161,11 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] / nB - a * M->iW[k] / nA);
-    const double term = rhof * Df * (M->W[k] / Wf) * dX;
-    const double Yf = 0.5 * (a / rA + b / rB);
+    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    const double term = rhof * Df * (M->W[k] * iWf) * dX;
+    const double Yf = 0.5 * (a * irA + b * irB);
     const double J = -term + Yf * corr;
-    const double hA = M->RW[k] * TA * hRTs(M, k, TA), hB = M->RW[k] * TB * hRTs(M, k, TB);
+    const double hA = M->RW[k] * TA * hRTi(M, k, TA, iTA), hB = M->RW[k] * TB * hRTi(M, k, TB, iTB);
     const double hfb = qnb * J;
     TAb += hfb * 0.5 * M->RW[k] * cpRa(M, k, TA);
     TBb += hfb * 0.5 * M->RW[k] * cpRa(M, k, TB);
@@ -170,28 +174,28 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   }
   // pass 3: back to the node's partial densities and diffusivities
   const double sgn = side ? 1.0 : -1.0;          // d(dX)/dX_B = +xf, d(dX)/dX_A = -xf
-  const double rn = side ? rB : rA, nn = side ? nB : nA;
+  const double rn = side ? rB : rA, inn = side ? inB : inA, irn = side ? irB : irA;
   const long long qn = side ? qB : qA;
   double rhofb = 0.0, Wfb = 0.0, nbar = 0.0, rbar = 0.0;
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB], an = U[k * N + qn];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] / nB - a * M->iW[k] / nA);
-    const double term = rhof * Df * (M->W[k] / Wf) * dX;
+    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    const double term = rhof * Df * (M->W[k] * iWf) * dX;
     const double termb = -Jb[k] + corrb;
     const double Yfb = Jb[k] * corr;
-    rhofb += termb * Df * (M->W[k] / Wf) * dX;
-    Wfb -= termb * term / Wf;
-    pb[PB_D + k] += 0.5 * termb * rhof * (M->W[k] / Wf) * dX;
-    const double Xb = sgn * termb * rhof * Df * M->W[k] / Wf * xf;
-    const double Xn = an * M->iW[k] / nn;
-    nbar -= Xb * Xn / nn;
-    rbar -= 0.5 * Yfb * an / (rn * rn);
-    ubar[k] += Xb * M->iW[k] / nn + 0.5 * Yfb / rn;
+    rhofb += termb * Df * (M->W[k] * iWf) * dX;
+    Wfb -= termb * term * iWf;
+    pb[PB_D + k] += 0.5 * termb * rhof * (M->W[k] * iWf) * dX;
+    const double Xb = sgn * termb * rhof * Df * (M->W[k] * iWf) * xf;
+    const double Xn = an * M->iW[k] * inn;
+    nbar -= Xb * Xn * inn;
+    rbar -= 0.5 * Yfb * an * (irn * irn);
+    ubar[k] += Xb * M->iW[k] * inn + 0.5 * Yfb * irn;
   }
-  rbar += 0.5 * Wfb / nn + 0.5 * rhofb;
-  nbar += -0.5 * Wfb * rn / (nn * nn);
+  rbar += 0.5 * Wfb * inn + 0.5 * rhofb;
+  nbar += -0.5 * Wfb * rn * (inn * inn);
 #pragma unroll
   for (int k = 0; k < NS; ++k) ubar[k] += rbar + nbar * M->iW[k];
   double mufb = -(2.0 / 3.0) * taub[d] * divu;
@@ -579,22 +583,17 @@ __global__ __launch_bounds__(BLK) void k_adj_diff(const MechTables* __restrict__
 }
 
 // ------------------------------------------------------------------ point
-// Deterministic block sum of one value per thread; every thread of the block
-// must call it (it contains barriers).
-__device__ __forceinline__ void block_sum_to(double v, double* wred, double* dst) {
+// Sum of one value per lane over the wavefront, in every lane (deterministic).
+__device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  if ((threadIdx.x & 63) == 0) wred[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double a = 0.0;
-    for (int w = 0; w < BLK / 64; ++w) a += wred[w];
-    *dst = a;
-  }
-  __syncthreads();
+  return v;
 }
 
-template <int NS>
+// Bound by FP64 instructions.  TAB: Omega11 and its derivative from the staged
+// tables (three passes over the pairs' four exponentials before: 343 against
+// 279 us at 64^3 cells, nine species).
+template <int NS, bool TAB>
 __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restrict__ M, const Member* __restrict__ mem,
                                                    int nmem, CallArgs A, const double* __restrict__ Ub,
                                                    const double* __restrict__ Tb, const double* __restrict__ pbb,
@@ -603,7 +602,14 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
                                                    double* __restrict__ thpart, int nth) {
   constexpr int NV = NS + 4, NPB = 8 + NS;
   __shared__ double conc[NS][BLK];
-  __shared__ double wred[BLK / 64];
+  // the parameters' sums per wavefront, added up once at the end
+  __shared__ double wred[4 + MAXNR][BLK / 64];
+  __shared__ alignas(16) double s_om[TAB ? OMROWS * (OMDEG + 1) : 2], s_dom[TAB ? OMROWS * (OMDEG + 1) : 2];
+  if constexpr (TAB) {
+    stage_om(s_om, M->om11, M->omrows);
+    stage_om(s_dom, M->dom11, M->omrows);
+    __syncthreads();
+  }
   const int m = find_member(mem, nmem, blockIdx.x);
   const Member& G = mem[m];
   const int tid = threadIdx.x;
@@ -670,7 +676,7 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
         double lnKc = M->dnu[j] * lnP;
 #pragma unroll
         for (int k = 0; k < NS; ++k) lnKc -= M->nunet[j][k] * Gs[k];
-        double rf = exp(lnkf), rbk = exp(lnkf - lnKc);
+        double rf = exp_sat(lnkf), rbk = exp_sat(lnkf - lnKc);
         for (int e = 0; e < M->nre[j]; ++e) {
           const double cc = conc[M->ridx[j][e]][tid];
           for (int kk = 0; kk < M->rnu[j][e]; ++kk) rf *= cc;
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
       }
     }
   }
-  // ---- phase 2: reverse of the reactions (every thread reaches the block sums)
+  // ---- phase 2: reverse of the reactions (every lane takes part in the wavefront sums)
   if (chem) {
     for (int j = 0; j < nr; ++j) {
       double lnkfb = 0.0;
@@ -710,7 +716,7 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
           lnKc -= M->nunet[j][k] * Gs[k];
           dlnKc += M->nunet[j][k] * hRTv[k] * iT;             // d G_k / dT = -hRT_k / T
         }
-        const double kf = exp(lnkf), kb = exp(lnkf - lnKc);
+        const double kf = exp_sat(lnkf), kb = exp_sat(lnkf - lnKc);
         double rf = kf, rbk = kb;
         for (int e = 0; e < M->nre[j]; ++e) {
           const double cc = conc[M->ridx[j][e]][tid];
@@ -749,10 +755,9 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
         const double lnKcb = qb * rbk;
         Tbar += lnkfb * (M->beta[j] * iT + M->EaR[j] * iT * iT) + lnKcb * dlnKc;
       }
-      block_sum_to(lnkfb, wred, &thpart[(long long)blockIdx.x * nth + 4 + j]);
+      lnkfb = wave_sum(lnkfb);
+      if ((tid & 63) == 0) wred[4 + j][tid >> 6] = lnkfb;
     }
-  } else if (tid == 0) {
-    for (int j = 0; j < nr; ++j) thpart[(long long)blockIdx.x * nth + 4 + j] = 0.0;
   }
   // ---- phase 3: transport, EOS, implicit Newton T, conserved variables
   double thE = 0.0, thx[3] = {0.0, 0.0, 0.0};
@@ -777,51 +782,69 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
 #pragma unroll
     for (int k = 0; k < NS; ++k) X[k] = Y[k] * Wm * M->iW[k];
     const double sqT = sqrt(T), T15 = T * sqT;
-    // Bird mixture diffusivities
+    // Bird mixture diffusivities, 1 / D_ij = (p / T^(3/2)) Omega11_ij iDpre_ij
     {
+      const int omr0 = M->omrow0, omrs = M->omrows;
+      auto omega = [&](int i, int j) { return omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[i][j]); };
+      // and its derivative by T
+      auto domega = [&](int i, int j) {
+        if constexpr (TAB) return omega11<TAB>(s_dom, omr0, omrs, T * M->Dieps[i][j]) * M->Dieps[i][j];
+        double dd;
+        om11a(lnT - M->Dlneps[i][j], T * M->Dieps[i][j], iT, M->Dieps[i][j], &dd);
+        return dd;
+      };
+      const double pT15 = p / T15;
       double Dacc[NS];
 #pragma unroll
       for (int k = 0; k < NS; ++k) Dacc[k] = 0.0;
+      // the pairs in order, each one's table rows read after the last one's use
+      constexpr Pairs<NS> PR;
 #pragma unroll
-      for (int i = 0; i < NS; ++i)
-#pragma unroll
-        for (int j = i + 1; j < NS; ++j) {
-          double dd;
-          const double om = om11a(lnT - M->Dlneps[i][j], T * M->Dieps[i][j], iT, M->Dieps[i][j], &dd);
-          const double iD = p * om / (M->Dpre[i][j] * T15);
-          Dacc[i] += fmax(X[j], 0.0) * iD;
-          Dacc[j] += fmax(X[i], 0.0) * iD;
-        }
+      for (int e = 0; e < Pairs<NS>::N; ++e) {
+        const int i = PR.i[e], j = PR.j[e];
+        double om = omega(i, j);
+        asm volatile("" : "+v"(om)::"memory");
+        const double iD = om * (pT15 * M->iDpre[i][j]);
+        Dacc[i] += fmax(X[j], 0.0) * iD;
+        Dacc[j] += fmax(X[i], 0.0) * iD;
+      }
       double Daccb[NS];
+      bool pure = false;   // a species alone in the mixture takes its self-diffusivity
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const double Db = pbv[(PB_D + k) * N + q];
-        if (Dacc[k] < 1e-300) {
-          double dd;
-          const double om = om11a(lnT - M->Dlneps[k][k], T * M->Dieps[k][k], iT, M->Dieps[k][k], &dd);
+        const bool alone = Dacc[k] < 1e-300;
+        pure = pure || alone;
+        const double iDa = alone ? 0.0 : 1.0 / Dacc[k];
+        Yb[k] += -Db * iDa;
+        Daccb[k] = -Db * ((1.0 - Y[k]) * iDa) * iDa;
+      }
+      if (pure) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          if (!(Dacc[k] < 1e-300)) continue;
+          const double Db = pbv[(PB_D + k) * N + q];
+          const double om = omega(k, k);
           const double Dk = M->Dpre[k][k] * T15 / (p * om);
           pbar += -Db * Dk / p;
-          Tbar += Db * Dk * (1.5 * iT - dd / om);
-          Daccb[k] = 0.0;
-        } else {
-          const double Dk = (1.0 - Y[k]) / Dacc[k];
-          Yb[k] += -Db / Dacc[k];
-          Daccb[k] = -Db * Dk / Dacc[k];
+          Tbar += Db * Dk * (1.5 * iT - domega(k, k) / om);
         }
       }
+      double S1 = 0.0, S2 = 0.0;   // sum of (1/D)bar / D, and of its part through Omega11
 #pragma unroll
-      for (int i = 0; i < NS; ++i)
-#pragma unroll
-        for (int j = i + 1; j < NS; ++j) {
-          double dd;
-          const double om = om11a(lnT - M->Dlneps[i][j], T * M->Dieps[i][j], iT, M->Dieps[i][j], &dd);
-          const double iD = p * om / (M->Dpre[i][j] * T15);
-          if (X[j] > 0.0) Xb[j] += Daccb[i] * iD;
-          if (X[i] > 0.0) Xb[i] += Daccb[j] * iD;
-          const double iDb = Daccb[i] * fmax(X[j], 0.0) + Daccb[j] * fmax(X[i], 0.0);
-          pbar += iDb * iD / p;
-          Tbar += iDb * iD * (dd / om - 1.5 * iT);
-        }
+      for (int e = 0; e < Pairs<NS>::N; ++e) {
+        const int i = PR.i[e], j = PR.j[e];
+        double om = omega(i, j), dd = domega(i, j);
+        asm volatile("" : "+v"(om), "+v"(dd)::"memory");
+        const double kD = pT15 * M->iDpre[i][j], iD = om * kD;
+        if (X[j] > 0.0) Xb[j] += Daccb[i] * iD;
+        if (X[i] > 0.0) Xb[i] += Daccb[j] * iD;
+        const double iDb = Daccb[i] * fmax(X[j], 0.0) + Daccb[j] * fmax(X[i], 0.0);
+        S1 += iDb * iD;
+        S2 += iDb * kD * dd;
+      }
+      pbar += S1 / p;
+      Tbar += S2 - 1.5 * iT * S1;
     }
     // Wilke viscosity and conductivity
     {
@@ -951,31 +974,41 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
       thx[2] = qLb * L.E * base * Ga[0] * Ga[1] * dGa[2];
     }
   }
-  // ---- phase 4: laser parameter partials (every thread)
-  block_sum_to(thE, wred, &thpart[(long long)blockIdx.x * nth + 0]);
-  block_sum_to(thx[0], wred, &thpart[(long long)blockIdx.x * nth + 1]);
-  block_sum_to(thx[1], wred, &thpart[(long long)blockIdx.x * nth + 2]);
-  block_sum_to(thx[2], wred, &thpart[(long long)blockIdx.x * nth + 3]);
+  // ---- phase 4: this block's parameter partials
+  thE = wave_sum(thE);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) thx[a] = wave_sum(thx[a]);
+  if ((tid & 63) == 0) {
+    wred[0][tid >> 6] = thE;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) wred[1 + a][tid >> 6] = thx[a];
+  }
+  __syncthreads();
+  if (tid < 4 + nr) {
+    double a = 0.0;
+    if (chem || tid < 4)
+      for (int w = 0; w < BLK / 64; ++w) a += wred[tid][w];
+    thpart[(long long)blockIdx.x * nth + tid] = a;
+  }
 }
 
-// One block per member: fixed-order sums of the parameter partials.
+// One block per member and parameter: fixed-order sums of the partials (the
+// parameters one after another in one block: 36 us at 1024 partials and 24
+// parameters).
 __global__ __launch_bounds__(BLK) void k_adj_theta(const Member* __restrict__ mem, const double* __restrict__ thpart,
                                                    int nth, double* __restrict__ pbar) {
   __shared__ double sh[BLK];
   const Member& G = mem[blockIdx.x];
-  const int tid = threadIdx.x;
-  for (int i = 0; i < nth; ++i) {
-    double a = 0.0;
-    for (int k = tid; k < G.nblocks; k += BLK) a += thpart[(long long)(G.block_begin + k) * nth + i];
-    sh[tid] = a;
-    __syncthreads();
-    for (int o = BLK / 2; o > 0; o >>= 1) {
-      if (tid < o) sh[tid] += sh[tid + o];
-      __syncthreads();
-    }
-    if (tid == 0) pbar[(long long)blockIdx.x * nth + i] += sh[0];
+  const int tid = threadIdx.x, i = blockIdx.y;
+  double a = 0.0;
+  for (int k = tid; k < G.nblocks; k += BLK) a += thpart[(long long)(G.block_begin + k) * nth + i];
+  sh[tid] = a;
+  __syncthreads();
+  for (int o = BLK / 2; o > 0; o >>= 1) {
+    if (tid < o) sh[tid] += sh[tid + o];
     __syncthreads();
   }
+  if (tid == 0) pbar[(long long)blockIdx.x * nth + i] += sh[0];
 }
 
 // y = a x + b y over n doubles (b = 0: y = a x)
@@ -989,7 +1022,7 @@ static hipError_t adj_t(const MechTables* M, const Member* mem, int nmem, int nb
                         const CallArgs& a,
                         const double* U, const double* T, const double* aux, const unsigned char* flag,
                         const unsigned char* bits, const double* lam, double s, double h, double* ubd, double* pbv,
-                        double* out, double* thpart, int nth, double psi_c, double CT, hipStream_t st) {
+                        double* out, double* thpart, int nth, double psi_c, double CT, bool om_tab, hipStream_t st) {
   hipLaunchKernelGGL((k_adj_conv_tiled<NS>), dim3(ntblocks), dim3(BLK), 0, st, mem, nmem, a, U, aux, flag, lam, s,
                      ubd, pbv, bits, psi_c, CT);
   hipError_t e = hipGetLastError();
@@ -999,8 +1032,12 @@ static hipError_t adj_t(const MechTables* M, const Member* mem, int nmem, int nb
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_adj_point<NS>, dim3(nblocks), dim3(BLK), 0, st, M, mem, nmem, a, U, T, pbv, ubd, lam, s, h, out,
-                     thpart, nth);
+  if (om_tab)
+    hipLaunchKernelGGL((k_adj_point<NS, true>), dim3(nblocks), dim3(BLK), 0, st, M, mem, nmem, a, U, T, pbv, ubd, lam,
+                       s, h, out, thpart, nth);
+  else
+    hipLaunchKernelGGL((k_adj_point<NS, false>), dim3(nblocks), dim3(BLK), 0, st, M, mem, nmem, a, U, T, pbv, ubd, lam,
+                       s, h, out, thpart, nth);
   return hipGetLastError();
 }
 
@@ -1008,23 +1045,18 @@ hipError_t launch_adjoint(int ns, const MechTables* M, const Member* mem, int nm
                           const CallArgs& a,
                           const double* U, const double* T, const double* aux, const unsigned char* flag,
                           const unsigned char* bits, const double* lam, double s, double h, double* ubd, double* pbv,
-                          double* out, double* thpart, int nth, double psi_c, double CT, hipStream_t st) {
+                          double* out, double* thpart, int nth, double psi_c, double CT, bool om_tab,
+                          hipStream_t st) {
 #define C_(NS)                                                                                                   \
   adj_t<NS>(M, mem, nmem, nblocks, ntblocks, a, U, T, aux, flag, bits, lam, s, h, ubd, pbv, out, thpart, nth, psi_c, \
-            CT, st)
-  switch (ns) {
-    case 1: return C_(1); case 2: return C_(2); case 3: return C_(3);
-    case 4: return C_(4); case 5: return C_(5); case 6: return C_(6);
-    case 7: return C_(7); case 8: return C_(8); case 9: return C_(9);
-    case 10: return C_(10); case 11: return C_(11); case 12: return C_(12);
-    default: return hipErrorInvalidValue;
-  }
+            CT, om_tab, st)
+  HTR_NS_SWITCH(ns, C_)
 #undef C_
 }
 
 hipError_t launch_adj_theta(const Member* mem, int nmem, const double* thpart, int nth, double* pbar,
                             hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_theta, dim3(nmem), dim3(BLK), 0, st, mem, thpart, nth, pbar);
+  hipLaunchKernelGGL(k_adj_theta, dim3(nmem, nth), dim3(BLK), 0, st, mem, thpart, nth, pbar);
   return hipGetLastError();
 }
 

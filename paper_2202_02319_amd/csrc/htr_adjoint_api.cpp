@@ -40,13 +40,7 @@ AdjBufs split(const htr_ctx* c, double* w) {
 htr_status rhs_adj(htr_ctx* c, const AdjBufs& b, const double* U, double* T, double tk, const htr_laser* laser,
                    const double* dlnA, const double* lam, double s, double h, double* out, double* pbar,
                    hipStream_t st, const TapeView* tv = nullptr) {
-  Ctx C{};
-  C.ns = c->ns;
-  C.M = c->dM;
-  C.mem = c->dmem;
-  C.nmem = 1;
-  C.nblocks = c->nblocks;
-  C.scheme = c->scheme;
+  const Ctx C = view(c);
   CallArgs a{};
   a.t = tk;
   a.use_call_laser = 1;
@@ -70,7 +64,7 @@ htr_status rhs_adj(htr_ctx* c, const AdjBufs& b, const double* U, double* T, dou
   }
   const int nth = 4 + c->nr;
   HIP_OK(launch_adjoint(C.ns, C.M, C.mem, 1, C.nblocks, c->ntblocks, a, U, Ts, aux, flag, bits, lam, s, h, b.ubd, b.pb,
-                        out, b.thpart, nth, C.scheme.psi_c, C.scheme.teno_CT, st));
+                        out, b.thpart, nth, C.scheme.psi_c, C.scheme.teno_CT, C.om_tab, st));
   HIP_OK(launch_adj_theta(C.mem, 1, b.thpart, nth, pbar, st));
   return HTR_OK;
 }

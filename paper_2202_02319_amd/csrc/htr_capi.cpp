@@ -66,8 +66,8 @@ htr_status check_laser(const htr_laser* L) {
   return HTR_OK;
 }
 
-// Tabulates Omega11 (the Neufeld-Janzen-Aziz fit) over the mechanism's range
-// of T* = T / (eps_ij / k): on each interval the Chebyshev interpolant of
+// Tabulates Omega11 (the Neufeld-Janzen-Aziz fit) and its derivative over the
+// mechanism's range of T* = T / (eps_ij / k): on each interval the Chebyshev interpolant of
 // degree OMDEG, formed in extended precision and stored as coefficients of
 // T* - centre.  The interval's half width is a 1/65 of T* at most, so the
 // fastest exponential, exp(-3.89411 T*), leaves a remainder below
@@ -99,6 +99,27 @@ static void tabulate_omega11(MechTables* T) {
   for (int i = 0; i < OMSUB; ++i)
     for (int k = 0; k < K; ++k)
       pm[i][k] = powl(1.0L + (2 * i + 1 + cs[2 * k + 1]) / (2.0L * OMSUB), -0.15610L);
+  // values at the Chebyshev nodes of an interval of half width h -> coefficients of (x - xc)
+  auto interpolate = [&](const long double* f, long double h, double* c) {
+    long double mono[K] = {}, t0[K] = {1.0L}, t1[K] = {0.0L, 1.0L};
+    for (int j = 0; j < K; ++j) {
+      long double ch = 0.0L;
+      for (int k = 0; k < K; ++k) ch += f[k] * cs[j * (2 * k + 1) % (4 * K)];
+      ch *= (j == 0 ? 1.0L : 2.0L) / K;
+      for (int k = 0; k < K; ++k) mono[k] += ch * t0[k];   // T_j in powers of (x - xc) / h
+      long double t2[K];
+      for (int k = 0; k < K; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
+      for (int k = 0; k < K; ++k) {
+        t0[k] = t1[k];
+        t1[k] = t2[k];
+      }
+    }
+    long double ih = 1.0L;
+    for (int k = 0; k < K; ++k) {
+      c[k] = (double)(mono[k] * ih);
+      ih /= h;
+    }
+  };
   int oct = INT_MIN;
   long double pe = 0.0L;
   for (int r = 0; r < n; ++r) {
@@ -115,27 +136,19 @@ static void tabulate_omega11(MechTables* T) {
         for (int k = 0; k < K; ++k) off[a][k] = amp[a] * expl(-rate[a] * h * cs[2 * k + 1]);
     }
     const long double ec[3] = {expl(-rate[0] * xc), expl(-rate[1] * xc), expl(-rate[2] * xc)};
-    long double f[K], ch[K], mono[K] = {}, t0[K] = {1.0L}, t1[K] = {0.0L, 1.0L};
-    for (int k = 0; k < K; ++k) f[k] = pe * pm[i][k] + ec[0] * off[0][k] + ec[1] * off[1][k] + ec[2] * off[2][k];
-    for (int j = 0; j < K; ++j) {
-      ch[j] = 0.0L;
-      for (int k = 0; k < K; ++k) ch[j] += f[k] * cs[j * (2 * k + 1) % (4 * K)];
-      ch[j] *= (j == 0 ? 1.0L : 2.0L) / K;
-    }
-    for (int j = 0; j < K; ++j) {   // the polynomials T_j in powers of (x - xc) / h
-      for (int k = 0; k < K; ++k) mono[k] += ch[j] * t0[k];
-      long double t2[K];
-      for (int k = 0; k < K; ++k) t2[k] = (k ? 2.0L * t1[k - 1] : 0.0L) - t0[k];
-      for (int k = 0; k < K; ++k) {
-        t0[k] = t1[k];
-        t1[k] = t2[k];
+    long double f[K], df[K];
+    for (int k = 0; k < K; ++k) {
+      const long double x = (long double)xc + h * cs[2 * k + 1], pw = pe * pm[i][k];
+      f[k] = pw;
+      df[k] = -0.15610L * pw / x;
+      for (int a = 0; a < 3; ++a) {
+        const long double ex = ec[a] * off[a][k];
+        f[k] += ex;
+        df[k] -= rate[a] * ex;
       }
     }
-    long double ih = 1.0L;
-    for (int k = 0; k < K; ++k) {
-      T->om11[r][k] = (double)(mono[k] * ih);
-      ih /= h;
-    }
+    interpolate(f, h, T->om11[r]);
+    interpolate(df, h, T->dom11[r]);
   }
   T->omrow0 = r0;
   T->omrows = n;

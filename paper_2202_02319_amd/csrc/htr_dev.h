@@ -63,7 +63,8 @@ struct MechTables {
   // octave, over [Tmin, Tmax] / (eps_ij / k); omrows = 0: the range needs
   // more than OMROWS intervals and the kernel evaluates the fit itself
   int omrow0, omrows;
-  double om11[OMROWS][OMDEG + 1];
+  alignas(16) double om11[OMROWS][OMDEG + 1];
+  alignas(16) double dom11[OMROWS][OMDEG + 1];   // d Omega11 / d T*
 };
 
 struct LaserDev {
@@ -284,7 +285,8 @@ hipError_t launch_adjoint(int ns, const MechTables* M, const Member* mem, int nm
                           const double* U, const double* T, const double* aux, const unsigned char* flag,
                           const unsigned char* bits,
                           const double* lam, double s, double h, double* ubd, double* pbv, double* out,
-                          double* thpart, int nth, double psi_c, double CT, hipStream_t st);
+                          double* thpart, int nth, double psi_c, double CT, bool om_tab,
+                          hipStream_t st);
 hipError_t launch_adj_theta(const Member* mem, int nmem, const double* thpart, int nth, double* pbar,
                             hipStream_t st);
 hipError_t launch_axpby(long long n, double a, const double* x, double b, double* y, hipStream_t st);
