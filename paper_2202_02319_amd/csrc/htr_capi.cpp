@@ -380,11 +380,10 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
     HIP_OK(launch_finalize(C.mem, C.nmem, w.blkred, C.scheme.cfl, dt_out, J_dev, a.dt_dev, jcoef, want_dt, t_adv, s));
   }
   if (C.curv) {
-    // curvilinear grid: mapped fluxes through per-face kernels, then the update
+    // curvilinear grid: mapped convective face fluxes, then the rest of the stage
     if (teno_bits) return fail(HTR_EUNSUPPORTED, "no tape on curvilinear grids");
     {
       TimedLaunch tl(C.timer, TC_SENSOR, s);
-      HIP_OK(launch_curv_igrad(C.ns, C.M, C.mem, C.nblocks, U, T, w.aux, C.cX, C.cdphi, s));
       HIP_OK(launch_curv_sensor(C.mem, C.nblocks, *C.curv, w.aux, C.ns, w.flag, C.scheme.theta_c, nullptr, s));
     }
     {
@@ -392,14 +391,10 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
       HIP_OK(launch_curv_conv(C.ns, *C.host1, C.mem, *C.curv, a, U, w.aux, w.flag, C.cffc, C.scheme.psi_c,
                               C.scheme.teno_CT, s));
     }
-    if (!(a.flags & HTR_VISC_OFF)) {
-      TimedLaunch tl(C.timer, TC_DIFF, s);
-      HIP_OK(launch_curv_diff(C.ns, C.M, C.mem, C.nblocks, *C.curv, U, T, w.aux, C.cX, C.cdphi, C.cffd, s));
-    }
     {
-      TimedLaunch tl(C.timer, TC_UPDATE, s);
-      HIP_OK(launch_curv_update(C.ns, C.mem, C.nblocks, *C.curv, a, U, Un, w.src, C.cffc, C.cffd, out, ca, cb,
-                                rhs_only, s));
+      TimedLaunch tl(C.timer, TC_DIFF, s);
+      HIP_OK(launch_curv_diff(C.ns, C.M, *C.host1, C.mem, *C.curv, a, U, Un, T, w.aux, w.src, C.cffc, out, ca, cb,
+                              rhs_only, s));
     }
     return HTR_OK;
   }
@@ -494,12 +489,8 @@ Ctx htr::view(const htr_ctx* c) {
   v.bounded = c->host_mem.bounded != 0;
   v.host1 = &c->host_mem;
   if (c->curv) {
-    const long long N = c->N;
     v.curv = &c->cg;
-    v.cX = c->dcw;
-    v.cdphi = c->dcw + (long long)c->ns * N;
-    v.cffc = v.cdphi + 3LL * (4 + c->ns) * N;
-    v.cffd = v.cffc + 3LL * (c->ns + 4) * N;
+    v.cffc = c->dcw;
   }
   return v;
 }
@@ -671,20 +662,22 @@ htr_status htr_create_curvilinear(const htr_mech_desc* mech, const htr_curv_grid
     return s2;
   };
   hipError_t e;
-  if ((e = hipMalloc(&c->dcurv, sizeof(double) * 22 * N)) != hipSuccess)
+  if ((e = hipMalloc(&c->dcurv, sizeof(double) * 49 * N)) != hipSuccess)
     return bail(fail(HTR_ENOMEM, "hipMalloc metrics: %s", hipGetErrorString(e)));
-  const long long nw = (long long)c->ns + 3LL * (4 + c->ns) + 6LL * (c->ns + 4);
+  const long long nw = 3LL * (c->ns + 4);
   if ((e = hipMalloc(&c->dcw, sizeof(double) * nw * N)) != hipSuccess)
     return bail(fail(HTR_ENOMEM, "hipMalloc curvilinear scratch: %s", hipGetErrorString(e)));
   double* mt = c->dcurv;
   double* mf = c->dcurv + 10 * N;
-  double* xyz = c->dcurv + 19 * N;
+  double* gf = c->dcurv + 19 * N;
+  double* xyz = c->dcurv + 46 * N;
   if ((e = hipMemcpy(xyz, grid->xyz, sizeof(double) * 3 * N, hipMemcpyHostToDevice)) != hipSuccess)
     return bail(fail(HTR_EDEVICE, "hipMemcpy coordinates: %s", hipGetErrorString(e)));
   g.mt = mt;
   g.mf = mf;
+  g.gf = gf;
   g.xyz = xyz;
-  if ((e = launch_curv_metrics(c->dmem, c->host_mem, g, mt, mf, nullptr)) != hipSuccess)
+  if ((e = launch_curv_metrics(c->dmem, c->host_mem, g, mt, mf, gf, nullptr)) != hipSuccess)
     return bail(fail(HTR_EDEVICE, "metric kernels: %s", hipGetErrorString(e)));
   std::vector<double> J(N);
   if ((e = hipMemcpy(J.data(), mt + 9 * N, sizeof(double) * N, hipMemcpyDeviceToHost)) != hipSuccess)

@@ -12,11 +12,9 @@
 // sum of commuting second differences, so a uniform flow stays uniform.
 //
 // Per stage: k_point (CURV variant: laser over lattice images, contravariant
-// dt limit, volume 1/J) -> mole fractions and index-space central
-// differences -> sensor -> convective and diffusive face kernels (all
-// directions in one launch each: the hybrid scheme on the metric-projected
-// flux; the diffusive flux by the chain rule) -> update.  These kernels are plain per-node/per-face
-// launches through L1/L2; the tiled LDS sweeps serve rectilinear grids.
+// dt limit, volume 1/J) -> sensor -> convective face kernel (the hybrid scheme
+// on the metric-projected flux, one launch per direction) -> diffusive flux by
+// the chain rule with the flux differences and the stage update, on tiles.
 #include <hip/hip_runtime.h>
 
 #include "htr_dev.h"
@@ -106,8 +104,11 @@ __global__ __launch_bounds__(BLK) void k_curv_metrics(const Member* __restrict__
   mt[9 * N + q] = (det > 0.0 && isfinite(det)) ? 1.0 / det : 0.0;
 }
 
+// Face values along d at row 9 d: mf the metric vector, gf the face mean of
+// d xi_e / d x_b (row 9 d + 3 k + b, axes e = d, d + 1, d + 2 in turn).
 __global__ __launch_bounds__(BLK) void k_curv_face_metrics(const Member* __restrict__ mem,
-                                                           const double* __restrict__ mt, double* __restrict__ mf) {
+                                                           const double* __restrict__ mt, double* __restrict__ mf,
+                                                           double* __restrict__ gf) {
   const Member& G = mem[0];
   const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
   if (q >= G.N) return;
@@ -125,6 +126,12 @@ __global__ __launch_bounds__(BLK) void k_curv_face_metrics(const Member* __restr
       double s = 0.0;
       for (int m = 0; m < 6; ++m) s += cw[m] * mt[(3 * d + c) * N + st[m]];
       mf[(3 * d + c) * N + q] = s / 60.0;
+    }
+    const double Ja = mt[9 * N + q], Jb = mt[9 * N + st[3]];
+    for (int k = 0; k < 3; ++k) {
+      const int e = (d + k) % 3;
+      for (int c = 0; c < 3; ++c)
+        gf[(9 * d + 3 * k + c) * N + q] = 0.5 * (Ja * mt[(3 * e + c) * N + q] + Jb * mt[(3 * e + c) * N + st[3]]);
     }
   }
 }
@@ -169,59 +176,6 @@ __global__ __launch_bounds__(BLK) void k_curv_sensor(const Member* __restrict__ 
   const double th = d2 / (d2 + wx * wx + wy * wy + wz * wz + 1e-300);
   flag[q] = th > theta_c ? 1 : 0;
   if (theta_out) theta_out[(nq - 1) * N + q] = th;
-}
-
-// Mole fractions X_s = Y_s W / W_s.
-template <int NS>
-__global__ __launch_bounds__(BLK) void k_curv_molefrac(const MechTables* __restrict__ M,
-                                                       const Member* __restrict__ mem, const double* __restrict__ U,
-                                                       double* __restrict__ X) {
-  const Member& G = mem[0];
-  const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
-  if (q >= G.N) return;
-  const long long N = G.N;
-  double r[NS], rho = 0.0;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    r[s] = U[s * N + q];
-    rho += r[s];
-  }
-  const double irho = 1.0 / rho;
-  double iW = 0.0;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) iW += r[s] * irho * M->iW[s];
-  const double W = 1.0 / iW;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) X[s * N + q] = r[s] * irho * W * M->iW[s];
-}
-
-// Index-space central differences (phi(i+1) - phi(i-1)) / 2 of
-// phi = (u, v, w, T, X_s) along each axis (zero along an inactive axis).
-template <int NS>
-__global__ __launch_bounds__(BLK) void k_curv_igrad(const Member* __restrict__ mem, const double* __restrict__ T,
-                                                    const double* __restrict__ aux, const double* __restrict__ X,
-                                                    double* __restrict__ dphi) {
-  constexpr int NP = 4 + NS;
-  const Member& G = mem[0];
-  const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
-  if (q >= G.N) return;
-  const long long N = G.N;
-  const int c[3] = {(int)(q % G.n[0]), (int)((q / G.n[0]) % G.n[1]), (int)(q / ((long long)G.n[0] * G.n[1]))};
-  const long long stride[3] = {1, G.n[0], (long long)G.n[0] * G.n[1]};
-  for (int a = 0; a < 3; ++a) {
-    double* out = dphi + (long long)a * NP * N;
-    if (!G.act[a]) {
-      for (int k = 0; k < NP; ++k) out[k * N + q] = 0.0;
-      continue;
-    }
-    const long long qp = q + (wrapi(c[a] + 1, G.n[a]) - c[a]) * stride[a];
-    const long long qm = q + (wrapi(c[a] - 1, G.n[a]) - c[a]) * stride[a];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) out[m * N + q] = (aux[(4 + m) * N + qp] - aux[(4 + m) * N + qm]) / 2.0;
-    out[3 * N + q] = (T[qp] - T[qm]) / 2.0;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) out[(4 + s) * N + q] = (X[s * N + qp] - X[s * N + qm]) / 2.0;
-  }
 }
 
 // Mapped convective flux through face i+1/2 along d, stored at node i: the
@@ -352,180 +306,359 @@ __global__ __launch_bounds__(BLK) void k_curv_conv(const Member* __restrict__ me
   }
 }
 
-// Mapped diffusive flux through face i+1/2 along d = blockIdx.y, stored at
-// node i: index-space derivatives at the face (normal from the two nodes,
-// tangential the mean of the two nodal central differences), physical
-// gradients by the chain rule with the face mean of d xi_e / d x, the flux
-// vector projected on the face metric vector n; arithmetic-mean face
-// coefficients.
-template <int NS>
-__global__ __launch_bounds__(BLK) void k_curv_diff(const MechTables* __restrict__ M, const Member* __restrict__ mem,
-                                                   CurvGeom g, const double* __restrict__ U,
-                                                   const double* __restrict__ T, const double* __restrict__ aux,
-                                                   const double* __restrict__ X, const double* __restrict__ dphi,
-                                                   double* __restrict__ ffd) {
-  constexpr int NV = NS + 4, NP = 4 + NS;
-  const Member& G = mem[0];
-  const int d = blockIdx.y;
-  if (!G.act[d]) return;
-  const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
-  if (q >= G.N) return;
-  const long long N = G.N;
-  const int c0[3] = {(int)(q % G.n[0]), (int)((q / G.n[0]) % G.n[1]), (int)(q / ((long long)G.n[0] * G.n[1]))};
-  int pb[3] = {c0[0], c0[1], c0[2]};
-  pb[d] = wrapi(c0[d] + 1, G.n[d]);
-  const long long qa = q, qb = lin(G, pb[0], pb[1], pb[2]);
-  const double n0 = g.mf[(3 * d) * N + q], n1 = g.mf[(3 * d + 1) * N + q], n2 = g.mf[(3 * d + 2) * N + q];
-  double* out = ffd + (long long)d * NV * N;
-  // ---- diffusive flux
-  const double nv3[3] = {n0, n1, n2};
-  double Gf[3][3];   // d xi_e / d x_b at the face
-  const double Ja = g.mt[9 * N + qa], Jb = g.mt[9 * N + qb];
-#pragma unroll
-  for (int e = 0; e < 3; ++e)
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-      Gf[e][b] = 0.5 * (Ja * g.mt[(3 * e + b) * N + qa] + Jb * g.mt[(3 * e + b) * N + qb]);
-  const double* dpa = dphi + qa;
-  const double* dpb = dphi + qb;
-  // derivative along index axis e at the face of phi row k (values va, vb at the two nodes)
-  auto dxi = [&](int k, int e, double va, double vb) -> double {
-    if (e == d) return vb - va;
-    if (!G.act[e]) return 0.0;
-    return 0.5 * (dpa[((long long)e * NP + k) * N] + dpb[((long long)e * NP + k) * N]);
-  };
-  double gu[3][3];   // gu[b][m] = d u_m / d x_b
-#pragma unroll
-  for (int m = 0; m < 3; ++m) {
-    const double va = aux[(4 + m) * N + qa], vb = aux[(4 + m) * N + qb];
-    double de[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e) de[e] = dxi(m, e, va, vb);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) gu[b][m] = Gf[0][b] * de[0] + Gf[1][b] * de[1] + Gf[2][b] * de[2];
-  }
-  double rhoA = 0.0, rhoB = 0.0;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    rhoA += U[s * N + qa];
-    rhoB += U[s * N + qb];
-  }
-  const double irA = 1.0 / rhoA, irB = 1.0 / rhoB;
-  double iWA = 0.0, iWB = 0.0;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    iWA += U[s * N + qa] * irA * M->iW[s];
-    iWB += U[s * N + qb] * irB * M->iW[s];
-  }
-  const double TA = T[qa], TB = T[qb];
-  const double mu = 0.5 * (aux[2 * N + qa] + aux[2 * N + qb]);
-  const double lam = 0.5 * (aux[3 * N + qa] + aux[3 * N + qb]);
-  const double rho = 0.5 * (rhoA + rhoB);
-  const double W = 0.5 * (1.0 / iWA + 1.0 / iWB);
-  const double divu = gu[0][0] + gu[1][1] + gu[2][2];
-  double tn[3];
-#pragma unroll
-  for (int m = 0; m < 3; ++m) {
-    tn[m] = 0.0;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      double tau = mu * (gu[b][m] + gu[m][b]);
-      if (b == m) tau -= (2.0 / 3.0) * mu * divu;
-      tn[m] += nv3[b] * tau;
-    }
-  }
-  // species: two passes (the correction flux first, then each species),
-  // recomputing the face normal derivative rather than holding per-species
-  // arrays, which keeps the kernel's register footprint small
-  auto rhoDW_dXn = [&](int s) -> double {
-    const double va = X[s * N + qa], vb = X[s * N + qb];
-    double de[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e) de[e] = dxi(4 + s, e, va, vb);
-    double dXn = 0.0;
-#pragma unroll
-    for (int b = 0; b < 3; ++b) dXn += (Gf[0][b] * de[0] + Gf[1][b] * de[1] + Gf[2][b] * de[2]) * nv3[b];
-    const double Df = 0.5 * (aux[(7 + s) * N + qa] + aux[(7 + s) * N + qb]);
-    return rho * Df * (M->W[s] / W) * dXn;
-  };
-  double corr = 0.0;
-#pragma unroll 1
-  for (int s = 0; s < NS; ++s) corr += rhoDW_dXn(s);
-  double gT[3];
-  {
-    double de[3];
-#pragma unroll
-    for (int e = 0; e < 3; ++e) de[e] = dxi(3, e, TA, TB);
-#pragma unroll
-    for (int b = 0; b < 3; ++b) gT[b] = Gf[0][b] * de[0] + Gf[1][b] * de[1] + Gf[2][b] * de[2];
-  }
-  double qn = -lam * (gT[0] * n0 + gT[1] * n1 + gT[2] * n2);
-#pragma unroll 1
-  for (int s = 0; s < NS; ++s) {
-    const double Yf = 0.5 * (U[s * N + qa] * irA + U[s * N + qb] * irB);
-    const double hf = 0.5 * (M->RW[s] * TA * hRTs(M, s, TA) + M->RW[s] * TB * hRTs(M, s, TB));
-    const double Jn = -rhoDW_dXn(s) + Yf * corr;
-    qn += Jn * hf;
-    out[s * N + q] = -Jn;
-  }
-  double work = 0.0;
-#pragma unroll
-  for (int m = 0; m < 3; ++m) work += tn[m] * 0.5 * (aux[(4 + m) * N + qa] + aux[(4 + m) * N + qb]);
-#pragma unroll
-  for (int m = 0; m < 3; ++m) out[(NS + m) * N + q] = tn[m];
-  out[(NS + 3) * N + q] = work - qn;
+// Tile of the diffusive kernel: BLK cells over the active axes.
+__host__ __device__ inline void curv_tile(const int act[3], int T[3]) {
+  const int na = (act[0] != 0) + (act[1] != 0) + (act[2] != 0);
+  for (int a = 0; a < 3; ++a) T[a] = na == 3 ? (a < 2 ? 8 : 4) : (act[a] ? (na == 2 ? 16 : BLK) : 1);
+  if (na == 0) T[0] = BLK;
 }
 
-// dU/dt = src + sum_d J ((Fd_d(i) - Fd_d(i - e_d)) - (Fc_d(i) - Fc_d(i - e_d)));
-// out = dU/dt (rhs_only) or the stage combination ca U^n + cb (U + dt dU/dt).
+// Mapped diffusive fluxes, their and the convective ones' differences, and the
+// stage update: dU/dt = src + J sum_d (F_d(i) - F_d(i - e_d)), F the diffusive
+// minus the convective flux; out = dU/dt (rhs_only) or the stage combination
+// ca U^n + cb (U + dt dU/dt).  The diffusive flux at a face: index-space
+// derivatives (normal from the two nodes, tangential the mean of the two nodal
+// central differences), physical gradients by the chain rule with gf, the flux
+// vector projected on the face metric vector; arithmetic-mean coefficients.
+//
+// One block per tile, one cell per thread: thread t has the lower face of its
+// cell along every axis, and the lanes of wavefront d + 1 the upper faces of
+// the tile's last layer along d.  The fields pass through LDS on the tile and
+// one layer around it (with its edges: the tangential differences), a few rows
+// at a time.  A species' normal derivatives are kept until the correction flux
+// is known, so its mole fraction is staged once.
+//
+// Bound by the latency of its staged phases at two blocks per CU (244
+// registers, 61 KB of LDS).  It takes 858 us at 128^3 cells and nine species;
+// mole fractions, index-space differences, face fluxes and update as four
+// launches through memory (about 330 values a cell written and read back) took
+// 65 + 258 + 1450 + 446 us.
+constexpr int CBOX = 10 * 10 * 6;   // a tile with its layer: 3-D the largest (2-D 18 x 18, 1-D 258)
 template <int NS>
-__global__ __launch_bounds__(BLK) void k_curv_update(const Member* __restrict__ mem, CurvGeom g, CallArgs A,
-                                                     const double* __restrict__ U, const double* __restrict__ Un,
-                                                     const double* __restrict__ src, const double* __restrict__ ffc,
-                                                     const double* __restrict__ ffd, double* __restrict__ out,
-                                                     double ca, double cb, int rhs_only) {
+__global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restrict__ M, const Member* __restrict__ mem,
+                                                      CurvGeom g, CallArgs A, const double* __restrict__ U,
+                                                      const double* Un, const double* __restrict__ Tf,
+                                                      const double* __restrict__ aux, const double* __restrict__ src,
+                                                      const double* __restrict__ ffc, double* out, double ca,
+                                                      double cb, int rhs_only) {
   constexpr int NV = NS + 4;
+  __shared__ double s_n[8][CBOX], s_F[3][3][DFACE];
   const Member& G = mem[0];
-  const long long q = (long long)blockIdx.x * BLK + threadIdx.x;
-  if (q >= G.N) return;
+  const int t = threadIdx.x;
   const long long N = G.N;
-  const int c[3] = {(int)(q % G.n[0]), (int)((q / G.n[0]) % G.n[1]), (int)(q / ((long long)G.n[0] * G.n[1]))};
-  const long long stride[3] = {1, G.n[0], (long long)G.n[0] * G.n[1]};
-  const double Jq = g.mt[9 * N + q];
-  double L[NV];
+  const bool act[3] = {G.act[0] != 0, G.act[1] != 0, G.act[2] != 0};
+  int T[3], nt[3], o[3];
+  curv_tile(G.act, T);
 #pragma unroll
-  for (int v = 0; v < NV; ++v) L[v] = v < NS ? src[v * N + q] : (v == NS + 3 ? src[NS * N + q] : 0.0);
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    if (!G.act[d]) continue;
-    const long long qm = q + (wrapi(c[d] - 1, G.n[d]) - c[d]) * stride[d];
-    const double* fc = ffc + (long long)d * NV * N;
-    const double* fd = ffd + (long long)d * NV * N;
-    if (A.flags & HTR_VISC_OFF) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) L[v] += Jq * (0.0 - (fc[v * N + q] - fc[v * N + qm]));
+  for (int a = 0; a < 3; ++a) nt[a] = (G.n[a] + T[a] - 1) / T[a];
+  tile_origin_of(T, nt, gridDim.x, blockIdx.x, o);
+  const int l[3] = {t % T[0], (t / T[0]) % T[1], t / (T[0] * T[1])};
+  const int gc[3] = {o[0] + l[0], o[1] + l[1], o[2] + l[2]};
+  const bool valid = gc[0] < G.n[0] && gc[1] < G.n[1] && gc[2] < G.n[2];
+  // grid index of the node at h in the tile (-1 .. T along an active axis)
+  auto node = [&](int h0, int h1, int h2) {
+    return lin(G, wrapi(o[0] + h0, G.n[0]), wrapi(o[1] + h1, G.n[1]), wrapi(o[2] + h2, G.n[2]));
+  };
+  const long long qc = node(l[0], l[1], l[2]);
+  const double Jc = g.mt[9 * N + qc], dt = rhs_only ? 0.0 : A.dt_dev[0];
+  struct Row { double s, u, un; };
+  auto row = [&](int v) {
+    return Row{v < NS ? src[v * N + qc] : (v == NS + 3 ? src[NS * N + qc] : 0.0), U[v * N + qc],
+               !rhs_only && ca != 0.0 ? Un[v * N + qc] : 0.0};
+  };
+  auto finish = [&](int v, const Row& r, double acc) {
+    if (!valid) return;
+    const double L = r.s + Jc * acc;
+    if (rhs_only) {
+      out[v * N + qc] = L;
     } else {
-#pragma unroll
-      for (int v = 0; v < NV; ++v)
-        L[v] += Jq * ((fd[v * N + q] - fd[v * N + qm]) - (fc[v * N + q] - fc[v * N + qm]));
+      const double base = r.u + dt * L;
+      out[v * N + qc] = ca != 0.0 ? ca * r.un + cb * base : cb * base;
     }
-  }
-  if (rhs_only) {
+  };
+  // lower nodes of this thread's faces: 0-2 along each axis, 3 the extra one
+  long long qf[4];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) out[v * N + q] = L[v];
+  for (int d = 0; d < 3; ++d) qf[d] = node(l[0] - (d == 0), l[1] - (d == 1), l[2] - (d == 2));
+  if (A.flags & HTR_VISC_OFF) {
+#pragma unroll 1
+    for (int v = 0; v < NV; ++v) {
+      const Row r = row(v);
+      double acc = 0.0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (act[d]) acc -= ffc[(d * NV + v) * N + qc] - ffc[(d * NV + v) * N + qf[d]];
+      finish(v, r, acc);
+    }
     return;
   }
-  const double dt = A.dt_dev[0];
-  double uv[NV], unv[NV];
+  // box: strides, this cell's slot, and this thread's nodes of the layer: one
+  // beside a face of the tile and one on its edges
+  const int p[3] = {act[0] ? 1 : 0, act[1] ? 1 : 0, act[2] ? 1 : 0};
+  const int st[3] = {p[0], p[1] ? T[0] + 2 * p[0] : 0, p[2] ? (T[0] + 2 * p[0]) * (T[1] + 2 * p[1]) : 0};
+  auto slot = [&](int h0, int h1, int h2) {
+    return p[0] * (h0 + 1) + st[1] * (h1 + 1) + st[2] * (h2 + 1);
+  };
+  const int sc = slot(l[0], l[1], l[2]);
+  int sh = sc, se = sc;
+  long long qh = qc, qe = qc;
+  bool has_h = false, has_e = false;
+  {
+    int k = t;   // the layers below and above along each axis
 #pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    uv[v] = U[v * N + q];
-    unv[v] = ca != 0.0 ? Un[v * N + q] : 0.0;
+    for (int d = 0; d < 3; ++d) {
+      const int S = BLK / T[d], cnt = p[d] ? 2 * S : 0;
+      if (k >= 0 && k < cnt) {
+        const int x = k % S, w = k < S ? -1 : T[d], Te = d == 0 ? T[1] : T[0];
+        const int x0 = x % Te, x1 = x / Te;
+        const int h0 = d == 0 ? w : x0, h1 = d == 1 ? w : (d == 0 ? x0 : x1), h2 = d == 2 ? w : x1;
+        qh = node(h0, h1, h2);
+        sh = slot(h0, h1, h2);
+        has_h = true;
+      }
+      k -= cnt;
+    }
+    k = t;   // the four edges along axis d, where the two others are active
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int a = d == 0 ? 1 : 0, b = d == 2 ? 1 : 2;
+      const int cnt = p[a] && p[b] ? 4 * T[d] : 0;
+      if (k >= 0 && k < cnt) {
+        const int x = k % T[d], c = k / T[d];
+        const int ha = c & 1 ? T[a] : -1, hb = c & 2 ? T[b] : -1;
+        const int h0 = d == 0 ? x : ha, h1 = d == 1 ? x : (d == 0 ? ha : hb), h2 = d == 2 ? x : hb;
+        qe = node(h0, h1, h2);
+        se = slot(h0, h1, h2);
+        has_e = true;
+      }
+      k -= cnt;
+    }
+  }
+  // the extra face's direction (one per wavefront), its slots and strides
+  const int xd = __builtin_amdgcn_readfirstlane(t >> 6) - 1, lane = t & 63;
+  const bool has_x = xd >= 0 && (xd == 0 ? act[0] : (xd == 1 ? act[1] : act[2])) &&
+                     lane < BLK / (xd == 0 ? T[0] : (xd == 1 ? T[1] : T[2]));
+  int sx = 0, xn = 0, x1 = 0, x2 = 0;
+  qf[3] = qc;
+  if (has_x) {
+    const int Te = xd == 0 ? T[1] : T[0];
+    const int y0 = lane % Te, y1 = lane / Te;
+    const int h0 = xd == 0 ? T[0] - 1 : y0, h1 = xd == 1 ? T[1] - 1 : (xd == 0 ? y0 : y1),
+              h2 = xd == 2 ? T[2] - 1 : y1;
+    sx = slot(h0, h1, h2);
+    qf[3] = node(h0, h1, h2);
+    xn = xd == 0 ? st[0] : (xd == 1 ? st[1] : st[2]);
+    x1 = xd == 0 ? st[1] : (xd == 1 ? st[2] : st[0]);
+    x2 = xd == 0 ? st[2] : (xd == 1 ? st[0] : st[1]);
+  }
+  const int pos[3] = {l[1] + T[1] * l[2], l[0] + T[0] * l[2], l[0] + T[0] * l[1]};
+  // where the upper face of this cell along d is in s_F[.][d]
+  const int up[3] = {l[0] + 1 < T[0] ? t + 1 : BLK + pos[0], l[1] + 1 < T[1] ? t + T[0] : BLK + pos[1],
+                     l[2] + 1 < T[2] ? t + T[0] * T[1] : BLK + pos[2]};
+  auto on = [&](int k) { return k < 3 ? act[k] : has_x; };
+  auto axis = [&](int k) { return k < 3 ? k : xd; };
+  // upper node's slot and the strides normal and tangential to face k
+  const int sB[4] = {sc, sc, sc, sx + xn};
+  const int sn[4] = {st[0], st[1], st[2], xn}, s1[4] = {st[1], st[2], st[0], x1}, s2[4] = {st[2], st[0], st[1], x2};
+  // derivative of a staged row along the face's three index axes
+  auto dxi = [&](const double* r, int k, double de[3]) {
+    const int b = sB[k], a = b - sn[k];
+    de[0] = r[b] - r[a];
+    de[1] = 0.25 * ((r[a + s1[k]] - r[a - s1[k]]) + (r[b + s1[k]] - r[b - s1[k]]));
+    de[2] = 0.25 * ((r[a + s2[k]] - r[a - s2[k]]) + (r[b + s2[k]] - r[b - s2[k]]));
+  };
+  auto mean = [&](const double* r, int k) { return 0.5 * (r[sB[k] - sn[k]] + r[sB[k]]); };
+  // rounds x before it meets another value (no operation of its own)
+  auto rounded = [](double x) {
+    asm("" : "+v"(x));
+    return x;
+  };
+  auto put = [&](int z, auto val) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (act[d]) s_F[z][d][t] = val(d);
+    if (has_x) s_F[z][xd][BLK + lane] = val(3);
+  };
+  auto difference = [&](int z, auto F) {
+    double acc = 0.0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (act[d]) acc += s_F[z][d][up[d]] - F(d);
+    return acc;
+  };
+  // convective flux of row v at face k
+  auto conv = [&](int v, int k) { return on(k) ? ffc[((long long)axis(k) * NV + v) * N + qf[k]] : 0.0; };
+  auto stage = [&](double* r, const double* f, bool edges) {
+    r[sc] = f[qc];
+    if (has_h) r[sh] = f[qh];
+    if (edges && has_e) r[se] = f[qe];
+  };
+  // velocity and viscosity
+#pragma unroll
+  for (int m = 0; m < 3; ++m) stage(s_n[m], aux + (4 + m) * N, true);
+  stage(s_n[3], aux + 2 * N, false);
+  double rc[NS], rh[NS], re[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    rc[s] = U[s * N + qc];
+    rh[s] = U[s * N + qh];
+    re[s] = U[s * N + qe];
+  }
+  double rhoc = 0.0, rhoh = 0.0, nc = 0.0, nh = 0.0, ne = 0.0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    rhoc += rc[s];
+    rhoh += rh[s];
+    nc += rc[s] * M->iW[s];
+    nh += rh[s] * M->iW[s];
+    ne += re[s] * M->iW[s];
+  }
+  const double inc = 1.0 / nc, inh = 1.0 / nh, ine = 1.0 / ne, irc = 1.0 / rhoc, irh = 1.0 / rhoh;
+  const double Tc = Tf[qc], Th = Tf[qh];
+  __syncthreads();
+  // a: the metric vector's components along the index gradients, so that
+  // n . grad phi = sum a d phi / d xi; tau: n . stress
+  double a[4][3], tau[4][3], en[4] = {}, k1[4] = {}, corr[4] = {};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    a[k][0] = a[k][1] = a[k][2] = tau[k][0] = tau[k][1] = tau[k][2] = 0.0;
+    if (!on(k)) continue;
+    const double* mf = g.mf + 3LL * axis(k) * N + qf[k];
+    const double* gp = g.gf + 9LL * axis(k) * N + qf[k];
+    double n[3], Gf[3][3], gu[3][3];   // gu[b][m] = d u_m / d x_b
+#pragma unroll
+    for (int b = 0; b < 3; ++b) n[b] = mf[b * N];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) Gf[e][b] = gp[(3 * e + b) * N];
+      a[k][e] = Gf[e][0] * n[0] + Gf[e][1] * n[1] + Gf[e][2] * n[2];
+    }
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      double de[3];
+      dxi(s_n[m], k, de);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) gu[b][m] = Gf[0][b] * de[0] + Gf[1][b] * de[1] + Gf[2][b] * de[2];
+    }
+    const double mu = mean(s_n[3], k), divu = gu[0][0] + gu[1][1] + gu[2][2];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      double x = 0.0;
+#pragma unroll
+      for (int b = 0; b < 3; ++b) x += n[b] * (gu[b][m] + gu[m][b]);
+      x = mu * (x - n[m] * ((2.0 / 3.0) * divu));
+      en[k] += x * mean(s_n[m], k);
+      tau[k][m] = rounded(x - conv(NS + m, k));
+    }
+  }
+  // conduction and the species' face factor rho / W
+  stage(s_n[4], Tf, true);
+  stage(s_n[5], aux + 3 * N, false);
+  s_n[6][sc] = rhoc;
+  s_n[7][sc] = rhoc * inc;
+  if (has_h) {
+    s_n[6][sh] = rhoh;
+    s_n[7][sh] = rhoh * inh;
+  }
+  Row mrow[3];
+#pragma unroll
+  for (int m = 0; m < 3; ++m) mrow[m] = row(NS + m);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) put(m, [&](int k) { return tau[k][m]; });
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!on(k)) continue;
+    double de[3];
+    dxi(s_n[4], k, de);
+    en[k] += mean(s_n[5], k) * (a[k][0] * de[0] + a[k][1] * de[1] + a[k][2] * de[2]);
+    k1[k] = mean(s_n[6], k) / mean(s_n[7], k);
   }
 #pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const double base = uv[v] + dt * L[v];
-    out[v * N + q] = ca != 0.0 ? ca * unv[v] + cb * base : cb * base;
+  for (int m = 0; m < 3; ++m) finish(NS + m, mrow[m], difference(m, [&](int d) { return tau[d][m]; }));
+  // species in twos, in alternating halves of the rows: rho D W_s / W n . grad X_s and their sum
+  double gx[NS][4];
+#pragma unroll
+  for (int s0 = 0; s0 < NS; s0 += 2) {
+    double(*R)[CBOX] = &s_n[(2 * s0) % 8];
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+      const int s = s0 + j;
+      R[2 * j][sc] = rc[s] * M->iW[s] * inc;
+      if (has_h) R[2 * j][sh] = rh[s] * M->iW[s] * inh;
+      if (has_e) R[2 * j][se] = re[s] * M->iW[s] * ine;
+      stage(R[2 * j + 1], aux + (7 + s) * N, false);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+        gx[s0 + j][k] = 0.0;
+        if (!on(k)) continue;
+        double de[3];
+        dxi(R[2 * j], k, de);
+        gx[s0 + j][k] = k1[k] * (M->W[s0 + j] * mean(R[2 * j + 1], k)) *
+                        (a[k][0] * de[0] + a[k][1] * de[1] + a[k][2] * de[2]);
+        corr[k] += gx[s0 + j][k];
+      }
+    }
+  }
+  // each species' flux and its enthalpy; the energy row goes with the last ones
+  const double iTc = 1.0 / Tc, iTh = 1.0 / Th;
+#pragma unroll
+  for (int s0 = 0; s0 < NS; s0 += 2) {
+    const bool last = s0 + 2 >= NS;
+    double(*R)[CBOX] = &s_n[(2 * (s0 + NS + (NS & 1))) % 8];
+    Row sr[2], er{};
+    double fc[2][4], fe[4] = {};
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+      sr[j] = row(s0 + j);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) fc[j][k] = conv(s0 + j, k);
+    }
+    if (last) {
+      er = row(NS + 3);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) fe[k] = conv(NS + 3, k);
+    }
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+      const int s = s0 + j;
+      R[2 * j][sc] = rc[s] * irc;
+      R[2 * j + 1][sc] = M->RW[s] * Tc * hRTi(M, s, Tc, iTc);
+      if (has_h) {
+        R[2 * j][sh] = rh[s] * irh;
+        R[2 * j + 1][sh] = M->RW[s] * Th * hRTi(M, s, Th, iTh);
+      }
+    }
+    __syncthreads();
+    double F[2][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int j = 0; j < 2 && s0 + j < NS; ++j) {
+        F[j][k] = 0.0;
+        if (!on(k)) continue;
+        const double f = gx[s0 + j][k] - mean(R[2 * j], k) * corr[k];
+        en[k] += f * mean(R[2 * j + 1], k);
+        F[j][k] = rounded(f - fc[j][k]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j) put(j, [&](int k) { return F[j][k]; });
+    if (last) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) en[k] = rounded(en[k] - fe[k]);
+      put(2, [&](int k) { return en[k]; });
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2 && s0 + j < NS; ++j)
+      finish(s0 + j, sr[j], difference(j, [&](int d) { return F[j][d]; }));
+    if (last) finish(NS + 3, er, difference(2, [&](int d) { return en[d]; }));
   }
 }
 
@@ -533,12 +666,12 @@ __global__ __launch_bounds__(BLK) void k_curv_update(const Member* __restrict__ 
 static inline int blocks_of(long long N) { return (int)((N + BLK - 1) / BLK); }
 
 hipError_t launch_curv_metrics(const Member* mem, const Member& host, const CurvGeom& g, double* mt, double* mf,
-                               hipStream_t s) {
+                               double* gf, hipStream_t s) {
   const int nb = blocks_of(host.N);
   hipLaunchKernelGGL(k_curv_metrics, dim3(nb), dim3(BLK), 0, s, mem, g, mt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_curv_face_metrics, dim3(nb), dim3(BLK), 0, s, mem, mt, mf);
+  hipLaunchKernelGGL(k_curv_face_metrics, dim3(nb), dim3(BLK), 0, s, mem, mt, mf, gf);
   return hipGetLastError();
 }
 
@@ -547,23 +680,6 @@ hipError_t launch_curv_sensor(const Member* mem, int nblocks, const CurvGeom& g,
   hipLaunchKernelGGL(k_curv_sensor, dim3(nblocks), dim3(BLK), 0, s, mem, g, aux, flag, theta_c, theta_out,
                      5 + 2 * ns + 3);
   return hipGetLastError();
-}
-
-template <int NS>
-static hipError_t igrad_t(const MechTables* M, const Member* mem, int nblocks, const double* U, const double* T,
-                          const double* aux, double* X, double* dphi, hipStream_t s) {
-  hipLaunchKernelGGL(k_curv_molefrac<NS>, dim3(nblocks), dim3(BLK), 0, s, M, mem, U, X);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_curv_igrad<NS>, dim3(nblocks), dim3(BLK), 0, s, mem, T, aux, X, dphi);
-  return hipGetLastError();
-}
-
-hipError_t launch_curv_igrad(int ns, const MechTables* M, const Member* mem, int nblocks, const double* U,
-                             const double* T, const double* aux, double* X, double* dphi, hipStream_t s) {
-#define C_(NS) igrad_t<NS>(M, mem, nblocks, U, T, aux, X, dphi, s)
-  HTR_NS_SWITCH(ns, C_)
-#undef C_
 }
 
 // Tiles of the convective face kernel: 64 x 4 faces in (x, y) when d is x,
@@ -600,35 +716,23 @@ hipError_t launch_curv_conv(int ns, const Member& host, const Member* mem, const
 }
 
 template <int NS>
-static hipError_t diff_t(const MechTables* M, const Member* mem, int nblocks, const CurvGeom& g, const double* U,
-                         const double* T, const double* aux, const double* X, const double* dphi, double* ffd,
+static hipError_t diff_t(const MechTables* M, const Member& host, const Member* mem, const CurvGeom& g,
+                         const CallArgs& a, const double* U, const double* Un, const double* T, const double* aux,
+                         const double* src, const double* ffc, double* out, double ca, double cb, int rhs_only,
                          hipStream_t s) {
-  hipLaunchKernelGGL(k_curv_diff<NS>, dim3(nblocks, 3), dim3(BLK), 0, s, M, mem, g, U, T, aux, X, dphi, ffd);
-  return hipGetLastError();
-}
-
-hipError_t launch_curv_diff(int ns, const MechTables* M, const Member* mem, int nblocks, const CurvGeom& g,
-                            const double* U, const double* T, const double* aux, const double* X,
-                            const double* dphi, double* ffd, hipStream_t s) {
-#define C_(NS) diff_t<NS>(M, mem, nblocks, g, U, T, aux, X, dphi, ffd, s)
-  HTR_NS_SWITCH(ns, C_)
-#undef C_
-}
-
-template <int NS>
-static hipError_t update_t(const Member* mem, int nblocks, const CurvGeom& g, const CallArgs& a, const double* U,
-                           const double* Un, const double* src, const double* ffc, const double* ffd, double* out,
-                           double ca, double cb, int rhs_only, hipStream_t s) {
-  hipLaunchKernelGGL(k_curv_update<NS>, dim3(nblocks), dim3(BLK), 0, s, mem, g, a, U, Un, src, ffc, ffd, out, ca, cb,
+  int td[3], nb = 1;
+  curv_tile(host.act, td);
+  for (int k = 0; k < 3; ++k) nb *= (host.n[k] + td[k] - 1) / td[k];
+  hipLaunchKernelGGL(k_curv_diff<NS>, dim3(nb), dim3(BLK), 0, s, M, mem, g, a, U, Un, T, aux, src, ffc, out, ca, cb,
                      rhs_only);
   return hipGetLastError();
 }
 
-hipError_t launch_curv_update(int ns, const Member* mem, int nblocks, const CurvGeom& g,
-                              const CallArgs& a, const double* U, const double* Un, const double* src,
-                              const double* ffc, const double* ffd, double* out, double ca, double cb, int rhs_only,
-                              hipStream_t s) {
-#define C_(NS) update_t<NS>(mem, nblocks, g, a, U, Un, src, ffc, ffd, out, ca, cb, rhs_only, s)
+hipError_t launch_curv_diff(int ns, const MechTables* M, const Member& host, const Member* mem, const CurvGeom& g,
+                            const CallArgs& a, const double* U, const double* Un, const double* T, const double* aux,
+                            const double* src, const double* ffc, double* out, double ca, double cb, int rhs_only,
+                            hipStream_t s) {
+#define C_(NS) diff_t<NS>(M, host, mem, g, a, U, Un, T, aux, src, ffc, out, ca, cb, rhs_only, s)
   HTR_NS_SWITCH(ns, C_)
 #undef C_
 }

@@ -122,6 +122,7 @@ __device__ __forceinline__ bool in_boundary_slab(const Member& G, const int c[3]
 struct CurvGeom {
   const double* mt;    // [10][N]: (d xi_d / d x_c) / J at row 3d + c; J at row 9
   const double* mf;    // [9][N]: the same at face i+1/2 along d
+  const double* gf;    // [27][N]: face means of d xi_e / d x_b at i+1/2 along d, row 9d + 3k + b, e = (d + k) mod 3
   const double* xyz;   // [3][N] node coordinates
   double P[3][3];      // P[a]: lattice displacement when index a advances by n[a]
   double Pinv[3][3];   // inverse of the matrix whose columns are P[a]
@@ -293,30 +294,24 @@ hipError_t launch_axpby(long long n, double a, const double* x, double b, double
 
 // Curvilinear grids (htr_curv.hip).  Metric terms of the node lattice
 // (xyz, P) into mt rows 0..8, J into row 9 (0 where det(d x / d xi) is not
-// positive and finite), face values into mf.
+// positive and finite), face values into mf and gf.
 hipError_t launch_curv_metrics(const Member* mem, const Member& host, const CurvGeom& g, double* mt, double* mf,
-                               hipStream_t s);
+                               double* gf, hipStream_t s);
 // Sensor flags (and theta into theta_out row nq - 1 when non-null) by the chain rule.
 hipError_t launch_curv_sensor(const Member* mem, int nblocks, const CurvGeom& g, const double* aux, int ns,
                               unsigned char* flag, double theta_c, double* theta_out, hipStream_t s);
-// Mole fractions X [ns][N] and index-space central differences of
-// (u, v, w, T, X_s) along each active axis, dphi [3][4 + ns][N].
-hipError_t launch_curv_igrad(int ns, const MechTables* M, const Member* mem, int nblocks, const double* U,
-                             const double* T, const double* aux, double* X, double* dphi, hipStream_t s);
-// Mapped face fluxes [3][ns + 4][N], face i+1/2 along d stored at node i:
-// convective (the hybrid scheme on the metric-projected flux) and diffusive.
+// Mapped convective face fluxes [3][ns + 4][N] (the hybrid scheme on the
+// metric-projected flux), face i+1/2 along d stored at node i.
 hipError_t launch_curv_conv(int ns, const Member& host, const Member* mem, const CurvGeom& g, const CallArgs& a,
                             const double* U, const double* aux, const unsigned char* flag, double* ffc, double psi_c,
                             double teno_CT, hipStream_t s);
-hipError_t launch_curv_diff(int ns, const MechTables* M, const Member* mem, int nblocks, const CurvGeom& g,
-                            const double* U, const double* T, const double* aux, const double* X,
-                            const double* dphi, double* ffd, hipStream_t s);
-// dU/dt = src + J sum_d ((ffd_d(i) - ffd_d(i - e_d)) - (ffc_d(i) - ffc_d(i - e_d)))
-// (ffd not read when HTR_VISC_OFF), then the stage combination as the
-// rectilinear sweep (or dU/dt itself when rhs_only).
-hipError_t launch_curv_update(int ns, const Member* mem, int nblocks, const CurvGeom& g,
-                              const CallArgs& a, const double* U, const double* Un, const double* src,
-                              const double* ffc, const double* ffd, double* out, double ca, double cb, int rhs_only,
-                              hipStream_t s);
+// dU/dt = src + J sum_d of the differences along d of (diffusive - convective)
+// face fluxes (no diffusive ones when HTR_VISC_OFF), then the stage
+// combination as the rectilinear sweep (or dU/dt itself when rhs_only).
+// out is not U.
+hipError_t launch_curv_diff(int ns, const MechTables* M, const Member& host, const Member* mem, const CurvGeom& g,
+                            const CallArgs& a, const double* U, const double* Un, const double* T, const double* aux,
+                            const double* src, const double* ffc, double* out, double ca, double cb, int rhs_only,
+                            hipStream_t s);
 
 }  // namespace htr

@@ -100,10 +100,7 @@ struct Ctx {
   // curvilinear single grid (null: rectilinear sweeps)
   const CurvGeom* curv = nullptr;
   const Member* host1 = nullptr;  // host copy of the single member (launch shapes of curvilinear and bounded grids)
-  double* cX = nullptr;           // [ns][N] mole fractions
-  double* cdphi = nullptr;        // [3][4 + ns][N] index-space central differences
   double* cffc = nullptr;         // [3][ns + 4][N] mapped convective face fluxes
-  double* cffd = nullptr;         // [3][ns + 4][N] mapped diffusive face fluxes
 };
 
 LaserDev make_laser(const htr_laser* L, const int n[3], const double Lp[3]);
@@ -171,8 +168,8 @@ struct htr_ctx {
   // distances between lattice planes (laser image counts)
   bool curv = false;
   htr::CurvGeom cg{};
-  double* dcurv = nullptr;         // mt [10][N], mf [9][N], xyz [3][N]
-  double* dcw = nullptr;           // X [ns][N], dphi [3][4 + ns][N], ffc and ffd [3][ns + 4][N]
+  double* dcurv = nullptr;         // mt [10][N], mf [9][N], gf [27][N], xyz [3][N]
+  double* dcw = nullptr;           // ffc [3][ns + 4][N]
 };
 
 // An ensemble (the opaque htr_batch of the C interface).
