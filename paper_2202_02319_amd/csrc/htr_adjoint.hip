@@ -256,7 +256,13 @@ __device__ __forceinline__ void adj_diff_tangential(const Member& G, const int c
 // hybrid decision and LF speed once, and for each variable its TENO cut-off
 // pattern once (four bits per side, in LDS).  Each node then gathers from
 // the six faces containing it: the face cotangent times the frozen linear
-// coefficient of its stencil position.
+// coefficient of its stencil position.  The Lax-Friedrichs speed's cotangent
+// is summed over the variables by the face and given to its argmax node at the
+// end.  Bound by latency at two blocks per CU: a variable's loads (values and
+// taped patterns) are issued while the one before is worked on.  280 us a
+// launch at 64^3 cells, nine species, taped; with the loads waited for in each
+// variable's turn and the speed's cotangent formed by every node of a face,
+// 460 us.
 constexpr int STGA = (EXTA + BLK - 1) / BLK;
 constexpr int FPTA = (FACEA + BLK - 1) / BLK;
 
@@ -306,11 +312,13 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
   // j-1 and j, whose stencil covers box positions fb_d .. fb_d + 5 along d
   int fe0[FPTA];
   long long fq[FPTA];   // the face's upper cell (index of the forward's taped cut-off patterns)
+  double fx[FPTA][2], fab[FPTA];   // metric of its two cells; cotangent of its Lax-Friedrichs speed
 #pragma unroll
   for (int k = 0; k < FPTA; ++k) {
     const int f = t + k * BLK;
     fe0[k] = -1;
     fq[k] = 0;
+    fab[k] = 0.0;
     if (f < F) {
       const int fb[3] = {f % FB[0], (f / FB[0]) % FB[1], f / (FB[0] * FB[1])};
       fe0[k] = fb[0] + B[0] * (fb[1] + B[1] * fb[2]);
@@ -343,6 +351,10 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
       }
       s_te[f] = (unsigned char)((te ? 1 : 0) | (am << 1));
       s_al[f] = al;
+      if (!te) fe0[k] = -1;   // nothing more to do for it
+      const int fd = d == 0 ? fb[0] : (d == 1 ? fb[1] : fb[2]);
+      fx[k][0] = G.xin[d][wrapi(o[d] + fd - 3, nd)];
+      fx[k][1] = G.xin[d][wrapi(o[d] + fd - 2, nd)];
     }
   }
   // node side: its box index, the six face slots containing it, the metric
@@ -374,7 +386,22 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
   for (int o7 = 0; o7 < 7; ++o7) xi7[o7] = G.xin[d][wrapi(gc[d] + o7 - 3, nd)];
   const double C6[6] = {1.0 / 60.0, -8.0 / 60.0, 37.0 / 60.0, 37.0 / 60.0, -8.0 / 60.0, 1.0 / 60.0};
   const double sg = s_ud[enode] < 0.0 ? -1.0 : 1.0;
-  double abar = 0.0;
+  // a variable's values and patterns are loaded while the one before is worked on
+  double nU[STGA], nL[STGA];
+  unsigned char nb[FPTA];
+  auto fetch = [&](int v) {
+#pragma unroll
+    for (int k = 0; k < STGA; ++k)
+      if (t + k * BLK < E) {
+        nU[k] = U[v * N + qe[k]];
+        nL[k] = lam[v * N + qe[k]];
+      }
+    if (tbits)
+#pragma unroll
+      for (int k = 0; k < FPTA; ++k)
+        if (fe0[k] >= 0) nb[k] = tbits[(long long)(d * NV + v) * N + fq[k]];
+  };
+  fetch(0);
   __syncthreads();
 #pragma unroll 1
   for (int v = 0; v < NV; ++v) {
@@ -382,34 +409,48 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
     for (int k = 0; k < STGA; ++k) {
       const int e = t + k * BLK;
       if (e < E) {
-        s_U[e] = U[v * N + qe[k]];
-        s_L[e] = s * lam[v * N + qe[k]];
+        s_U[e] = nU[k];
+        s_L[e] = s * nL[k];
       }
     }
+    if (tbits)
+#pragma unroll
+      for (int k = 0; k < FPTA; ++k)
+        if (fe0[k] >= 0) s_db[t + k * BLK] = nb[k];
     __syncthreads();
-    // faces: cut-off bits of the TENO faces
+    if (v + 1 < NV) fetch(v + 1);
+    if (!tbits) {
+      // faces: cut-off bits of the TENO faces
+#pragma unroll
+      for (int k = 0; k < FPTA; ++k) {
+        if (fe0[k] < 0) continue;
+        const int f = t + k * BLK, e0 = fe0[k];
+        const double al = s_al[f];
+        double hp[6], hm[6];
+#pragma unroll
+        for (int mm = 0; mm < 6; ++mm) {
+          const int e = e0 + mm * bs;
+          const double u6 = s_U[e], f6 = node_flux<NS>(v, d, u6, s_ud[e], s_p[e]);
+          hp[mm] = fma(al, u6, f6);
+          hm[5 - mm] = fma(-al, u6, f6);
+        }
+        s_db[f] = (unsigned char)(teno6_decide(hp, CT) | (teno6_decide(hm, CT) << 4));
+      }
+      __syncthreads();
+    }
+    // the speed's cotangent, once per face
 #pragma unroll
     for (int k = 0; k < FPTA; ++k) {
       if (fe0[k] < 0) continue;
-      const int f = t + k * BLK;
-      if (!(s_te[f] & 1)) continue;
-      if (tbits) {
-        s_db[f] = tbits[(long long)(d * NV + v) * N + fq[k]];
-        continue;
-      }
       const int e0 = fe0[k];
-      const double al = s_al[f];
-      double hp[6], hm[6];
+      const unsigned bits = s_db[t + k * BLK];
+      const double* cp = s_cf[bits & 15u];
+      const double* cm = s_cf[bits >> 4];
+      double da = 0.0;
 #pragma unroll
-      for (int mm = 0; mm < 6; ++mm) {
-        const int e = e0 + mm * bs;
-        const double u6 = s_U[e], f6 = node_flux<NS>(v, d, u6, s_ud[e], s_p[e]);
-        hp[mm] = fma(al, u6, f6);
-        hm[5 - mm] = fma(-al, u6, f6);
-      }
-      s_db[f] = (unsigned char)(teno6_decide(hp, CT) | (teno6_decide(hm, CT) << 4));
+      for (int mm = 0; mm < 6; ++mm) da += (cp[mm] - cm[5 - mm]) * s_U[e0 + mm * bs];
+      fab[k] += (fx[k][1] * s_L[e0 + 3 * bs] - fx[k][0] * s_L[e0 + 2 * bs]) * 0.5 * da;
     }
-    __syncthreads();
     if (valid) {
       double Fb = 0.0, Ub = 0.0;
 #pragma unroll
@@ -444,14 +485,6 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
               }
             }
           }
-          // the Lax-Friedrichs speed's frozen argmax node receives d(|u_d| + c)
-          if ((pos[k] >> (te >> 1)) & 1u) {
-            const int e0 = enode + (k - 5) * bs;   // the face's stencil start
-            double da = 0.0;
-#pragma unroll
-            for (int mm = 0; mm < 6; ++mm) da += (cp[mm] - cm[5 - mm]) * s_U[e0 + mm * bs];
-            abar += g * 0.5 * da;
-          }
         }
       }
       const double un = s_ud[enode], un_u = s_U[enode], un_p = s_p[enode];
@@ -467,7 +500,19 @@ __device__ __forceinline__ void adj_conv_tiled_dir(const Member& G, const int o[
     }
     __syncthreads();
   }
+  // a Lax-Friedrichs speed's frozen argmax node receives d(|u_d| + c)
+#pragma unroll
+  for (int k = 0; k < FPTA; ++k)
+    if (fe0[k] >= 0) s_U[t + k * BLK] = fab[k];
+  __syncthreads();
   if (valid) {
+    double abar = 0.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const int f = f0 + k * fs;
+      const unsigned te = s_te[f];
+      if (((use >> k) & te & 1u) && ((pos[k] >> (te >> 1)) & 1u)) abar += s_U[f];
+    }
     pbu += abar * sg;
     pbc += abar;
   }
