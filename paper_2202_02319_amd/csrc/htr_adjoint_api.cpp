@@ -59,7 +59,7 @@ htr_status rhs_adj(htr_ctx* c, const AdjBufs& b, const double* U, double* T, dou
   } else {
     HIP_OK(launch_point(C.ns, C.M, C.mem, 1, C.nblocks, 0, a, U, T, c->ws.aux, c->ws.src, nullptr, nullptr, nullptr,
                         c->ws.status, 0, C.om_tab, st));
-    HIP_OK(launch_sensor(C.mem, 1, C.nblocks, 0, c->ws.aux, C.ns, c->ws.flag, c->ws.grad, C.scheme.theta_c,
+    HIP_OK(launch_sensor(C.mem, 1, C.nblocks, 0, nullptr, c->ws.aux, C.ns, c->ws.flag, c->ws.grad, C.scheme.theta_c,
                          nullptr, st));
   }
   const int nth = 4 + c->nr;

@@ -364,7 +364,7 @@ TimedLaunch::~TimedLaunch() {
   }
 }
 
-// One RHS evaluation at stage time t + tcoef*dt: point -> [reduce] -> sensor -> sweep.
+// One RHS evaluation at stage time t + tcoef*dt: point -> sensor (with the reduction) -> sweeps.
 // want_dt: the per-cell kernel also reduces the stable step and writes dt_dev.
 htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const double* U, const double* Un,
                  double* T, double* out, double ca, double cb, int rhs_only, double* hrr, double* J_dev,
@@ -375,11 +375,12 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
     HIP_OK(launch_point(C.ns, C.M, C.mem, C.nmem, C.nblocks, C.grid, a, U, T, w.aux, w.src, hrr,
                         need_red ? w.blkred : nullptr, nullptr, w.status, want_dt, C.om_tab, s, C.curv));
   }
-  if (need_red) {
-    TimedLaunch tl(C.timer, TC_REDUCE, s);
-    HIP_OK(launch_finalize(C.mem, C.nmem, w.blkred, C.scheme.cfl, dt_out, J_dev, a.dt_dev, jcoef, want_dt, t_adv, s));
-  }
+  const Reduction red{w.blkred, C.scheme.cfl, dt_out, J_dev, a.dt_dev, jcoef, want_dt, t_adv};
   if (C.curv) {
+    if (need_red) {
+      TimedLaunch tl(C.timer, TC_REDUCE, s);
+      HIP_OK(launch_finalize(C.mem, C.nmem, red, s));
+    }
     // curvilinear grid: mapped convective face fluxes, then the rest of the stage
     if (teno_bits) return fail(HTR_EUNSUPPORTED, "no tape on curvilinear grids");
     {
@@ -400,8 +401,8 @@ htr_status stage(const Ctx& C, const Workspace& w, const CallArgs& a, const doub
   }
   {
     TimedLaunch tl(C.timer, TC_SENSOR, s);
-    HIP_OK(launch_sensor(C.mem, C.nmem, C.nblocks, C.grid, w.aux, C.ns, w.flag, w.grad, C.scheme.theta_c, nullptr,
-                         s));
+    HIP_OK(launch_sensor(C.mem, C.nmem, C.nblocks, C.grid, need_red ? &red : nullptr, w.aux, C.ns, w.flag, w.grad,
+                         C.scheme.theta_c, nullptr, s));
   }
   {
     TimedLaunch tl(C.timer, TC_CONV, s);
@@ -798,7 +799,8 @@ htr_status htr_cells(htr_ctx* c, const double* U, double* T_io, double t, const 
   if (C.curv)
     HIP_OK(launch_curv_sensor(C.mem, C.nblocks, *C.curv, c->ws.aux, C.ns, c->ws.flag, C.scheme.theta_c, out, s));
   else
-    HIP_OK(launch_sensor(C.mem, 1, C.nblocks, 0, c->ws.aux, C.ns, c->ws.flag, c->ws.grad, C.scheme.theta_c, out, s));
+    HIP_OK(launch_sensor(C.mem, 1, C.nblocks, 0, nullptr, c->ws.aux, C.ns, c->ws.flag, c->ws.grad, C.scheme.theta_c,
+                         out, s));
   return HTR_OK;
 }
 
@@ -812,7 +814,8 @@ htr_status htr_stable_dt(htr_ctx* c, const double* U, double* T_io, double* dt_d
   hipStream_t s = (hipStream_t)stream;
   HIP_OK(launch_point(C.ns, C.M, C.mem, 1, C.nblocks, 0, a, U, T_io, c->ws.aux, c->ws.src, nullptr, c->ws.blkred,
                       nullptr, c->ws.status, 1, C.om_tab, s, C.curv));
-  HIP_OK(launch_finalize(C.mem, 1, c->ws.blkred, c->scheme.cfl, dt_dev, nullptr, nullptr, 0.0, 1, nullptr, s));
+  HIP_OK(launch_finalize(C.mem, 1, Reduction{c->ws.blkred, c->scheme.cfl, dt_dev, nullptr, nullptr, 0.0, 1, nullptr},
+                         s));
   return HTR_OK;
 }
 

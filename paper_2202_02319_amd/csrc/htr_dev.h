@@ -241,9 +241,23 @@ hipError_t launch_point(int ns, const MechTables* M, const Member* mem, int nmem
                         const double* U, double* T, double* aux, double* src, double* hrr, double* blkred,
                         double* cells_out, unsigned* status, int want_dt, bool om_tab, hipStream_t s,
                         const CurvGeom* cg = nullptr);
-hipError_t launch_sensor(const Member* mem, int nmem, int nblocks, int grid, const double* aux, int ns,
-                         unsigned char* flag,
-                         double* grad, double theta_c, double* theta_out, hipStream_t s);
+// What follows from the per-cell kernel's block partials, per member: the step
+// cfl * min (want_dt, else dt_in where given), J += jcoef * dt * sum and
+// t_adv += dt, the last two where not null.
+struct Reduction {
+  const double* blkred;
+  double cfl;
+  double* dt_dev;
+  double* J_dev;
+  const double* dt_in;
+  double jcoef;
+  int want_dt;
+  double* t_adv;
+};
+// red (nullable): the stage's reduction, by blocks of the same launch.
+hipError_t launch_sensor(const Member* mem, int nmem, int nblocks, int grid, const Reduction* red, const double* aux,
+                         int ns, unsigned char* flag, double* grad, double theta_c, double* theta_out,
+                         hipStream_t s);
 // bits (nullable): TENO cut-off patterns [3][nv][N] bytes, per axis, variable
 // and face (indexed by the face's upper cell); written for TENO faces only.
 // tcls: one byte per tile (at least ntblocks), the lean sweep's tile marks;
@@ -273,10 +287,7 @@ void set_tiles(Member& M, const int* shape, int* tblocks, int* dtblocks);
 bool tile_shape_ok(const int act[3], const int shape[3], const char** why);
 // Default tile shape for the active axes.
 void default_tile_shape(const int act[3], int shape[3]);
-// t_adv (nullable): per-member time to advance by the step.
-hipError_t launch_finalize(const Member* mem, int nmem, const double* blkred, double cfl, double* dt_dev,
-                           double* J_dev, const double* dt_in, double jcoef, int want_dt, double* t_adv,
-                           hipStream_t s);
+hipError_t launch_finalize(const Member* mem, int nmem, const Reduction& red, hipStream_t s);
 hipError_t launch_advance_time(int nmem, double* t_dev, const double* dt_dev, hipStream_t s);
 hipError_t launch_member_max(const Member* mem, int nmem, const double* field, double* out, int accumulate,
                              hipStream_t s);
