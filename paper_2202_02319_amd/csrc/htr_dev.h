@@ -285,8 +285,8 @@ hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem,
 void set_tiles(Member& M, const int* shape, int* tblocks, int* dtblocks);
 // Whether a tile shape suits a member with active axes act (message on failure).
 bool tile_shape_ok(const int act[3], const int shape[3], const char** why);
-// Default tile shape for the active axes.
-void default_tile_shape(const int act[3], int shape[3]);
+// Default tile shape for the active axes of a grid of n cells.
+void default_tile_shape(const int act[3], const int n[3], int shape[3]);
 hipError_t launch_finalize(const Member* mem, int nmem, const Reduction& red, hipStream_t s);
 hipError_t launch_advance_time(int nmem, double* t_dev, const double* dt_dev, hipStream_t s);
 hipError_t launch_member_max(const Member* mem, int nmem, const double* field, double* out, int accumulate,

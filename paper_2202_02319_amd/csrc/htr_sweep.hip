@@ -27,11 +27,26 @@ namespace htr {
 // Tile shapes of the tiled kernels: 256 cells.  Default 16 x 4 x 4 on 3-D
 // grids, 16 x 16 over the two active axes of 2-D grids, 256 along a 1-D
 // grid; other shapes are accepted if every staging buffer holds them.
-void default_tile_shape(const int act[3], int t[3]) {
+// In 3-D the shape whose tiles cost least in all, a ragged tile as much as a
+// whole one: the weights are a step's time at 128^3 cells, where every shape
+// divides the grid, against 16x4x4 (7.09 ms; 7.24, 7.27 and 7.67 ms: shorter
+// rows along x).  83x61x37 cells have 960 tiles of 16x4x4 and 880 of 8x8x4: a
+// step takes 2.17 against 1.98 ms; 64 members of 12 to 24 cells an axis, 8.0
+// against 7.35 ms.
+void default_tile_shape(const int act[3], const int n[3], int t[3]) {
   const int na = act[0] + act[1] + act[2];
   t[0] = t[1] = t[2] = 1;
   if (na == 3) {
-    t[0] = 16; t[1] = 4; t[2] = 4;
+    constexpr int shapes[4][3] = {{16, 4, 4}, {8, 8, 4}, {8, 4, 8}, {4, 8, 8}};
+    constexpr int weight[4] = {100, 102, 103, 108};
+    long long best = 0;
+    for (int k = 0; k < 4; ++k) {
+      long long w = weight[k];
+      for (int a = 0; a < 3; ++a) w *= (n[a] + shapes[k][a] - 1) / shapes[k][a];
+      if (k > 0 && w >= best) continue;
+      best = w;
+      for (int a = 0; a < 3; ++a) t[a] = shapes[k][a];
+    }
   } else if (na == 2) {
     for (int a = 0; a < 3; ++a) t[a] = act[a] ? 16 : 1;
   } else if (na == 1) {
@@ -68,9 +83,9 @@ bool tile_shape_ok(const int act[3], const int t[3], const char** why) {
 // The diffusive sweep's tile for the active axes: 8 x 8 x 4 in 3-D (its 256
 // halo nodes are one per thread); for k_diff_flat 16 x 12 over the two active
 // axes of a 2-D grid (204 and 208 faces) and 192 along a 1-D grid.
-static void diff_tile_shape(const int act[3], int t[3]) {
+static void diff_tile_shape(const int act[3], const int n[3], int t[3]) {
   const int na = act[0] + act[1] + act[2];
-  default_tile_shape(act, t);
+  default_tile_shape(act, n, t);
   if (na == 3) {
     t[0] = 8; t[1] = 8; t[2] = 4;
   } else if (na == 2) {
@@ -89,7 +104,7 @@ void set_tiles(Member& M, const int* shape, int* tblocks, int* dtblocks) {
   if (shape) {
     t[0] = shape[0]; t[1] = shape[1]; t[2] = shape[2];
   } else {
-    default_tile_shape(act, t);
+    default_tile_shape(act, M.n, t);
   }
   int nb = 1;
   for (int a = 0; a < 3; ++a) {
@@ -101,7 +116,7 @@ void set_tiles(Member& M, const int* shape, int* tblocks, int* dtblocks) {
   M.ntblocks = nb;
   *tblocks += nb;
   int dt[3];
-  diff_tile_shape(act, dt);
+  diff_tile_shape(act, M.n, dt);
   int nd = 1;
   for (int a = 0; a < 3; ++a) {
     M.dtdim[a] = dt[a];

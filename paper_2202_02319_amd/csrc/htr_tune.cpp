@@ -45,7 +45,8 @@ std::vector<std::array<int, 3>> shape_candidates(const int act[3]) {
     }
   } else {
     int t[3];
-    default_tile_shape(act, t);
+    const int n[3] = {1, 1, 1};   // one shape, whatever the size
+    default_tile_shape(act, n, t);
     raw.push_back({t[0], t[1], t[2]});
   }
   for (auto& t : raw)
@@ -152,7 +153,7 @@ htr_status htr_set_tiling(htr_ctx* c, const int32_t shape[3], int32_t grid) {
     for (int a = 0; a < 3; ++a) t[a] = shape[a];
   } else {
     const int act[3] = {c->host_mem.act[0], c->host_mem.act[1], c->host_mem.act[2]};
-    default_tile_shape(act, t);
+    default_tile_shape(act, c->host_mem.n, t);
   }
   c->ntblocks = 0;
   c->ndtblocks = 0;
@@ -229,7 +230,7 @@ htr_status htr_batch_set_tiling(htr_batch* b, int32_t member, const int32_t shap
       if (st) return st;
       for (int a = 0; a < 3; ++a) t[a] = shape[a];
     } else {
-      default_tile_shape(act, t);
+      default_tile_shape(act, M.n, t);
     }
     for (int a = 0; a < 3; ++a) M.tdim[a] = t[a];
   }
