@@ -328,9 +328,11 @@ __host__ __device__ inline void curv_tile(const int act[3], int T[3]) {
 // at a time.  A species' normal derivatives are kept until the correction flux
 // is known, so its mole fraction is staged once.
 //
-// Bound by the latency of its staged phases at two blocks per CU (244
-// registers, 61 KB of LDS).  It takes 858 us at 128^3 cells and nine species;
-// mole fractions, index-space differences, face fluxes and update as four
+// Bound by the latency of its staged phases at two blocks per CU (250
+// registers, 61 KB of LDS); each group of loads is issued a group ahead (766 us
+// at 128^3 cells and nine species, 858 with each waited for in its turn; the
+// metrics a face ahead as well: no change).
+// Mole fractions, index-space differences, face fluxes and update as four
 // launches through memory (about 330 values a cell written and read back) took
 // 65 + 258 + 1450 + 446 us.
 constexpr int CBOX = 10 * 10 * 6;   // a tile with its layer: 3-D the largest (2-D 18 x 18, 1-D 258)
@@ -564,6 +566,14 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
   Row mrow[3];
 #pragma unroll
   for (int m = 0; m < 3; ++m) mrow[m] = row(NS + m);
+  // a group's loads are issued before the one ahead of it is worked on
+  double Dc[NS], Dh[NS];
+  auto fetchD = [&](int s) {
+    Dc[s] = aux[(7 + s) * N + qc];
+    Dh[s] = aux[(7 + s) * N + qh];
+  };
+  fetchD(0);
+  if (NS > 1) fetchD(1);
 #pragma unroll
   for (int m = 0; m < 3; ++m) put(m, [&](int k) { return tau[k][m]; });
   __syncthreads();
@@ -588,9 +598,12 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
       R[2 * j][sc] = rc[s] * M->iW[s] * inc;
       if (has_h) R[2 * j][sh] = rh[s] * M->iW[s] * inh;
       if (has_e) R[2 * j][se] = re[s] * M->iW[s] * ine;
-      stage(R[2 * j + 1], aux + (7 + s) * N, false);
+      R[2 * j + 1][sc] = Dc[s];
+      if (has_h) R[2 * j + 1][sh] = Dh[s];
     }
     __syncthreads();
+#pragma unroll
+    for (int j = 2; j < 4 && s0 + j < NS; ++j) fetchD(s0 + j);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
 #pragma unroll
@@ -607,18 +620,23 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
   }
   // each species' flux and its enthalpy; the energy row goes with the last ones
   const double iTc = 1.0 / Tc, iTh = 1.0 / Th;
+  Row sr[NS];
+  double fc[NS][4];
+  auto fetch = [&](int s) {
+    sr[s] = row(s);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) fc[s][k] = conv(s, k);
+  };
+  fetch(0);
+  if (NS > 1) fetch(1);
 #pragma unroll
   for (int s0 = 0; s0 < NS; s0 += 2) {
     const bool last = s0 + 2 >= NS;
     double(*R)[CBOX] = &s_n[(2 * (s0 + NS + (NS & 1))) % 8];
-    Row sr[2], er{};
-    double fc[2][4], fe[4] = {};
+    Row er{};
+    double fe[4] = {};
 #pragma unroll
-    for (int j = 0; j < 2 && s0 + j < NS; ++j) {
-      sr[j] = row(s0 + j);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) fc[j][k] = conv(s0 + j, k);
-    }
+    for (int j = 2; j < 4 && s0 + j < NS; ++j) fetch(s0 + j);
     if (last) {
       er = row(NS + 3);
 #pragma unroll
@@ -644,7 +662,7 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
         if (!on(k)) continue;
         const double f = gx[s0 + j][k] - mean(R[2 * j], k) * corr[k];
         en[k] += f * mean(R[2 * j + 1], k);
-        F[j][k] = rounded(f - fc[j][k]);
+        F[j][k] = rounded(f - fc[s0 + j][k]);
       }
     }
 #pragma unroll
@@ -657,7 +675,7 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 2 && s0 + j < NS; ++j)
-      finish(s0 + j, sr[j], difference(j, [&](int d) { return F[j][d]; }));
+      finish(s0 + j, sr[s0 + j], difference(j, [&](int d) { return F[j][d]; }));
     if (last) finish(NS + 3, er, difference(2, [&](int d) { return en[d]; }));
   }
 }
