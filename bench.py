@@ -75,8 +75,8 @@ def point_bytes_per_cell(ns):
 
 CSRC = os.path.join(ROOT, "paper_2202_02319_amd", "csrc")
 KERNEL_SOURCES = {
-    "k_point": ("htr_point.hip", "htr_dev.h", "htr_flux.h"),
-    "k_sensor": ("htr_point.hip", "htr_dev.h", "htr_flux.h"),
+    "k_point": ("htr_point.hip", "htr_dev.h", "htr_flux.h", "htr_math.h"),
+    "k_sensor": ("htr_point.hip", "htr_dev.h", "htr_flux.h", "htr_math.h"),
     "k_conv": ("htr_sweep.hip", "htr_dev.h", "htr_flux.h"),
     "k_diff": ("htr_sweep.hip", "htr_dev.h", "htr_flux.h"),
 }
@@ -521,7 +521,7 @@ def main():
                     help="with --no-autotune: 1 runs central tiles in the lean convective sweep (the default), "
                          "0 every tile in the full sweep")
     ap.add_argument("--tile", type=str, default=None,
-                    help="with --no-autotune: the convective tile shape, e.g. 8x8x4 (default 16x4x4)")
+                    help="with --no-autotune: the convective tile shape, e.g. 8x8x4 (default: by the grid)")
     ap.add_argument("--calib-copy", action="store_true",
                     help="end with a plain 1 GiB device copy (scale for HBM byte counters)")
     args = ap.parse_args()
