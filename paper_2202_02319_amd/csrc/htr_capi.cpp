@@ -728,7 +728,8 @@ htr_status htr_set_boundaries(htr_ctx* c, const int32_t bc[3][2], const double p
       return fail(HTR_EINVAL, "axis %d: unknown boundary type", a);
     if ((lo == HTR_BC_PERIODIC) != (hi == HTR_BC_PERIODIC))
       return fail(HTR_EINVAL, "axis %d: periodic on one side only", a);
-    if (lo != HTR_BC_PERIODIC && c->n[a] < 8) return fail(HTR_EINVAL, "axis %d: a bounded axis needs n >= 8", a);
+    if (lo != HTR_BC_PERIODIC && c->n[a] < BNDMIN)
+      return fail(HTR_EINVAL, "axis %d: a bounded axis needs n >= %d", a, BNDMIN);
     for (int side = 0; side < 2; ++side) {
       if (bc[a][side] == HTR_BC_OUTFLOW && !(pinf[a][side] > 0 && relax[a][side] >= 0 && std::isfinite(relax[a][side])))
         return fail(HTR_EINVAL, "axis %d side %d: outflow needs p_inf > 0 and relax >= 0", a, side);

@@ -107,6 +107,7 @@ struct Member {
   int bounded;                // any axis bounded
 };
 
+constexpr int BNDMIN = 8;   // nodes that a bounded axis has at least
 // Whether cell coordinate c lies within three nodes of a bounded boundary:
 // the cells whose right-hand side the boundary kernel writes.
 __device__ __forceinline__ bool in_boundary_slab(const Member& G, const int c[3]) {

@@ -1500,8 +1500,17 @@ template <int NS>
 static hipError_t bnd_t(const MechTables* M, const Member* mem, const Member& host, const CallArgs& a, const double* U,
                         const double* T, const double* aux, const double* src, const unsigned char* flag,
                         const double* grad, double* part, double psi_c, double CT, hipStream_t s) {
+  // the blocks of the slab there is; under capture those of the largest one, as
+  // the launch keeps its size while htr_set_boundaries may bound another axis
+  // before a replay (the kernel takes the types from the device's member, and
+  // its blocks past the slab do nothing)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(s, &capture);
+  if (e != hipSuccess) return e;
+  int bc[3][2];
+  for (int b = 0; b < 3; ++b) bc[b][0] = bc[b][1] = capture == hipStreamCaptureStatusNone ? host.bc[b][0] : host.n[b] >= BNDMIN;
   long long cells = 0;
-  for (int b = 0; b < 3; ++b) cells += slab_cells(host.n, host.bc, b);
+  for (int b = 0; b < 3; ++b) cells += slab_cells(host.n, bc, b);
   const unsigned nblocks = (unsigned)((cells + BNDC - 1) / BNDC);
   hipLaunchKernelGGL(k_bnd<NS>, dim3(nblocks), dim3(6 * BNDC), 0, s, M, mem, a, U, T, aux, src, flag, grad, part, psi_c, CT);
   return hipGetLastError();

@@ -1,0 +1,68 @@
+"""A captured step follows htr_set_boundaries: replays after the boundary types
+change (more bounded axes than at the capture, fewer, none) against eager steps
+of a context created with those types, bit for bit (the same kernels on the same
+state).  The library's sources compiled for the CPU."""
+import numpy as np
+import pytest
+import torch
+
+import cpu_build
+import synth
+from oracle import Oracle
+from paper_2202_02319_amd import htr
+
+W, I, O = synth.BC_WALL, synth.BC_INFLOW, synth.BC_OUTFLOW
+P, WW, OO = (0, 0), (W, W), (O, O)
+NS = 5
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    mp = pytest.MonkeyPatch()
+    yield cpu_build.use(cpu_build.build(tmp_path_factory.mktemp("cpu"), [NS]), mp)
+    mp.undo()
+
+
+class _Run:
+    def __init__(self, case, bc, U0):
+        case.bc, case.pinf, case.relax = bc, ((101325.0,) * 2,) * 3, ((0.25,) * 2,) * 3
+        self.g, self.case = htr.Context.from_case(case), case
+        self.U, self.T = torch.tensor(U0), torch.tensor(case.T)
+        self.t, self.dt, self.J = (torch.zeros(1, dtype=torch.float64) for _ in range(3))
+        self.work = torch.empty(self.g.work_bytes() // 8, dtype=torch.float64)
+
+    def step(self):
+        htr.htr_rk3_step(self.g, self.U, self.T, self.t, self.dt, 1, self.case.laser, None, self.work, self.J)
+
+    def state(self):
+        return [x.clone() for x in (self.U, self.T, self.t, self.dt, self.J)]
+
+    def restore(self, s):
+        for x, y in zip((self.U, self.T, self.t, self.dt, self.J), s):
+            x.copy_(y)
+
+
+@pytest.mark.parametrize("n,captured,then", [
+    ((13, 9, 8), (OO, P, P), [(OO, WW, P), ((I, O), WW, OO), (P, P, OO)]),
+    ((9, 8, 7), (P, WW, P), [(OO, OO, P), (P, P, P), (OO, P, P)]),
+    ((24, 17, 1), (P, WW, P), [(OO, WW, P), (OO, P, P)]),
+])
+def test_replays(lib, n, captured, then):
+    case = synth.small_case(n=n, seed=5, mech=synth.case_c1().mech)
+    case.vel *= 0.0
+    U0 = Oracle(case).prim_to_cons()
+    r = _Run(case, captured, U0)
+    start = r.state()
+    lib.cpu_capture_begin()
+    r.step()
+    graph = lib.cpu_capture_end()
+    for bc in [captured] + then + [captured]:
+        e = _Run(case, bc, U0)
+        htr.htr_set_boundaries(r.g, bc, case.pinf, case.relax)
+        r.restore(start)
+        for _ in range(2):
+            lib.cpu_replay(graph)
+            e.step()
+            for a, b in zip(r.state(), e.state()):
+                assert np.array_equal(a, b), bc
+        htr.htr_check(r.g)
