@@ -137,6 +137,13 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   const double inA = 1.0 / nA, inB = 1.0 / nB, irA = 1.0 / rA, irB = 1.0 / rB;
   const double Wf = 0.5 * (rA * inA + rB * inB), iWf = 1.0 / Wf;
   const double TA = T[qA], TB = T[qB], iTA = 1.0 / TA, iTB = 1.0 / TB;
+  // both mole fractions rounded before they are differenced (no FMA across the
+  // difference), as in the forward sweep: a uniform composition gives exactly zero
+  auto dXf = [&](int k, double a, double b) {
+#pragma clang fp contract(off)
+    const double XA = a * M->iW[k] * inA, XB = b * M->iW[k] * inB;
+    return XB - XA;
+  };
   // pass 1: corr = sum_k term_k (per-species values are recomputed from
   // cached loads in every pass instead of being held in registers)
   double corr = 0.0;
@@ -144,7 +151,7 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    const double dX = xf * dXf(k, a, b);
     corr += rhof * Df * (M->W[k] * iWf) * dX;
   }
   // ---- reverse
@@ -161,7 +168,7 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    const double dX = xf * dXf(k, a, b);
     const double term = rhof * Df * (M->W[k] * iWf) * dX;
     const double Yf = 0.5 * (a * irA + b * irB);
     const double J = -term + Yf * corr;
@@ -181,7 +188,7 @@ __device__ __forceinline__ void adj_diff_face(const MechTables* __restrict__ M, 
   for (int k = 0; k < NS; ++k) {
     const double a = U[k * N + qA], b = U[k * N + qB], an = U[k * N + qn];
     const double Df = 0.5 * (aux[(7 + k) * N + qA] + aux[(7 + k) * N + qB]);
-    const double dX = xf * (b * M->iW[k] * inB - a * M->iW[k] * inA);
+    const double dX = xf * dXf(k, a, b);
     const double term = rhof * Df * (M->W[k] * iWf) * dX;
     const double termb = -Jb[k] + corrb;
     const double Yfb = Jb[k] * corr;

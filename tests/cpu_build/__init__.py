@@ -41,7 +41,7 @@ def build(out, species):
 
     def compile_(src):
         obj = os.path.join(out, os.path.basename(src) + ".o")
-        subprocess.run([CLANG, "-std=c++17", "-O1", "-fPIC", "-w", "-mfma", "-ffp-contract=fast", "-x", "c++", "-I", HERE,
+        subprocess.run([CLANG, "-std=c++17", "-O1", "-fPIC", "-w", "-mfma", "-ffp-contract=fast-honor-pragmas", "-x", "c++", "-I", HERE,
                         "-I", os.path.join(ROOT, "include"), "-I", out, "-c", src, "-o", obj], check=True)
         return obj
     with ThreadPoolExecutor(max_workers=8) as ex:

@@ -17,10 +17,13 @@ NS = 5
 
 
 @pytest.fixture(scope="module")
-def lib(tmp_path_factory):
-    mp = pytest.MonkeyPatch()
-    yield cpu_build.use(cpu_build.build(tmp_path_factory.mktemp("cpu"), [NS]), mp)
-    mp.undo()
+def built(tmp_path_factory):
+    return cpu_build.build(tmp_path_factory.mktemp("cpu"), [NS])
+
+
+@pytest.fixture
+def lib(built, monkeypatch):
+    return cpu_build.use(built, monkeypatch)
 
 
 class _Run:
