@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstdio>
@@ -207,6 +208,9 @@ htr_status build_tables(const htr_mech_desc* m, MechTables* T) {
     T->qW[s] = std::pow(W, -0.25);
   }
   T->lnP0 = std::log(PREF / RU);
+  T->Tguess = 1.0;
+  for (int s = 0; s < ns; ++s) T->Tguess = std::fmax(T->Tguess, std::fabs(T->hc[s][5]));
+  T->Tguess /= DBL_MAX;
   for (int i = 0; i < ns; ++i)
     for (int j = 0; j < ns; ++j) {
       const double Wi = m->W[i], Wj = m->W[j];

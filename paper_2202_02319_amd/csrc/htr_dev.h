@@ -56,6 +56,7 @@ struct MechTables {
   double imu_pre[MAXNS];                   // 1 / mu_pre
   double rsW[MAXNS], qW[MAXNS];            // sqrt(W), W^(-1/4)
   double lnP0;                             // ln(p_ref / R_u)
+  double Tguess;                           // |T| above which 1/T and hc[s][5] / T are finite for every species
   int nfac[MAXNR];                         // factors of the longer side of a reaction's rates
   int rfac[MAXNR][SIDE * 3];               // species of each factor of the forward rate (ns: the factor one)
   int pfac[MAXNR][SIDE * 3];

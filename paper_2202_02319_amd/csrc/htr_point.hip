@@ -188,7 +188,9 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
       auto newton = [&](double T) {
         return (T * (H0 + T * (H1 + T * (H2 + T * (H3 + T * H4)))) - Rm * T + e0) * rcp_nr(cp_mix(T) - Rm);
       };
-      for (int it = 0; it < 50; ++it) {
+      // a guess that h/(RT) is not finite at (zero among them) is refused
+      const int most = fabs(T) > M->Tguess ? 50 : 0;
+      for (int it = 0; it < most; ++it) {
         const double dT = newton(T);
         T -= dT;
         if (!isfinite(T) || !(T > 0.0)) break;
