@@ -60,8 +60,8 @@ __device__ __forceinline__ double om22a(double x, double Ts, double iT, double i
   *dT = -0.14874 * e0 * iT - (0.77320 * e1 + 2.43787 * e2) * ieps;
   return e0 + e1 + e2;
 }
-__device__ __forceinline__ double om11a(double x, double Ts, double iT, double ieps, double* dT) {
-  const double e0 = 1.06036 * exp(-0.15610 * x), e1 = 0.19300 * exp(-0.47635 * Ts);
+__device__ __forceinline__ double om11a(double pw, double Ts, double iT, double ieps, double* dT) {   // pw = Ts^(-0.1561)
+  const double e0 = 1.06036 * pw, e1 = 0.19300 * exp(-0.47635 * Ts);
   const double e2 = 1.03587 * exp(-1.52996 * Ts), e3 = 1.76474 * exp(-3.89411 * Ts);
   *dT = -0.15610 * e0 * iT - (0.47635 * e1 + 1.52996 * e2 + 3.89411 * e3) * ieps;
   return e0 + e1 + e2 + e3;
@@ -837,13 +837,18 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
     // Bird mixture diffusivities, 1 / D_ij = (p / T^(3/2)) Omega11_ij iDpre_ij
     {
       const int omr0 = M->omrow0, omrs = M->omrows;
-      auto omega = [&](int i, int j) { return omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[i][j]); };
+      const double Tb11 = TAB ? 0.0 : exp_in(-0.15610 * lnT);
+      auto omega = [&](int i, int j) {
+        return omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[i][j], TAB ? 0.0 : Tb11 * M->pw11[i][j]);
+      };
       // and its derivative by T
-      auto domega = [&](int i, int j) {
-        if constexpr (TAB) return omega11<TAB>(s_dom, omr0, omrs, T * M->Dieps[i][j]) * M->Dieps[i][j];
-        double dd;
-        om11a(lnT - M->Dlneps[i][j], T * M->Dieps[i][j], iT, M->Dieps[i][j], &dd);
-        return dd;
+      auto omega_dT = [&](int i, int j, double* dd) {
+        if constexpr (TAB) {
+          *dd = omega11<TAB>(s_dom, omr0, omrs, T * M->Dieps[i][j], 0.0) * M->Dieps[i][j];
+          return omega(i, j);
+        } else {
+          return om11a(Tb11 * M->pw11[i][j], T * M->Dieps[i][j], iT, M->Dieps[i][j], dd);
+        }
       };
       const double pT15 = p / T15;
       double Dacc[NS];
@@ -855,7 +860,7 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
       for (int e = 0; e < Pairs<NS>::N; ++e) {
         const int i = PR.i[e], j = PR.j[e];
         double om = omega(i, j);
-        asm volatile("" : "+v"(om)::"memory");
+        if constexpr (TAB) asm volatile("" : "+v"(om)::"memory");
         const double iD = om * (pT15 * M->iDpre[i][j]);
         Dacc[i] += fmax(X[j], 0.0) * iD;
         Dacc[j] += fmax(X[i], 0.0) * iD;
@@ -876,18 +881,19 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
         for (int k = 0; k < NS; ++k) {
           if (!(Dacc[k] < 1e-300)) continue;
           const double Db = pbv[(PB_D + k) * N + q];
-          const double om = omega(k, k);
+          double dd;
+          const double om = omega_dT(k, k, &dd);
           const double Dk = M->Dpre[k][k] * T15 / (p * om);
           pbar += -Db * Dk / p;
-          Tbar += Db * Dk * (1.5 * iT - domega(k, k) / om);
+          Tbar += Db * Dk * (1.5 * iT - dd / om);
         }
       }
       double S1 = 0.0, S2 = 0.0;   // sum of (1/D)bar / D, and of its part through Omega11
 #pragma unroll
       for (int e = 0; e < Pairs<NS>::N; ++e) {
         const int i = PR.i[e], j = PR.j[e];
-        double om = omega(i, j), dd = domega(i, j);
-        asm volatile("" : "+v"(om), "+v"(dd)::"memory");
+        double dd, om = omega_dT(i, j, &dd);
+        if constexpr (TAB) asm volatile("" : "+v"(om), "+v"(dd)::"memory");
         const double kD = pT15 * M->iDpre[i][j], iD = om * kD;
         if (X[j] > 0.0) Xb[j] += Daccb[i] * iD;
         if (X[i] > 0.0) Xb[i] += Daccb[j] * iD;

@@ -71,10 +71,11 @@ struct Pairs {
 constexpr int OMPF = 3;
 // Neufeld-Janzen-Aziz collision integral Omega11(T*): from the staged table
 // (row = the top bits of T*, a polynomial in T* - the interval's centre), or
-// the fit itself.  The table's eight coefficients are four 16-byte LDS reads
-// and seven FMAs where the fit takes four exponentials.
+// the fit itself, pw = T*^(-0.1561) its power (a product of a factor per cell and
+// one per pair).  The table's eight coefficients are four 16-byte LDS reads and
+// seven FMAs where the fit takes three exponentials.
 template <bool TAB>
-__device__ __forceinline__ double omega11(const double* __restrict__ s_om, int row0, int rows, double Ts) {
+__device__ __forceinline__ double omega11(const double* __restrict__ s_om, int row0, int rows, double Ts, double pw) {
   if constexpr (TAB) {
     const int hi = __double2hiint(Ts);
     const unsigned row = min((unsigned)((hi >> 15) - row0), (unsigned)(rows - 1));
@@ -85,8 +86,7 @@ __device__ __forceinline__ double omega11(const double* __restrict__ s_om, int r
     for (int k = OMDEG - 1; k >= 0; --k) v = fma(v, t, c[k]);
     return v;
   } else {
-    return 1.06036 * exp(-0.15610 * log(Ts)) + 0.19300 * exp(-0.47635 * Ts) + 1.03587 * exp(-1.52996 * Ts) +
-           1.76474 * exp(-3.89411 * Ts);
+    return 1.06036 * pw + 0.19300 * exp(-0.47635 * Ts) + 1.03587 * exp(-1.52996 * Ts) + 1.76474 * exp(-3.89411 * Ts);
   }
 }
 

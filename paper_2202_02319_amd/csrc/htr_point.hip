@@ -266,6 +266,10 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
     for (int s = 0; s < NS; ++s) Dacc[s] = 0.0;
     const double T15 = T * sqT, pT15 = p / T15;
     const int omr0 = M->omrow0, omrs = M->omrows;
+    const double Tb11 = TAB ? 0.0 : exp_in(-0.15610 * lnT);   // the fit's power factors as Omega22's does
+    auto omega = [&](int i, int j) {
+      return omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[i][j], TAB ? 0.0 : Tb11 * M->pw11[i][j]);
+    };
     // the pairs (i < j) in groups of OMPF, each group's integrals formed before
     // the next group's table rows are read: left alone, the compiler reads
     // every pair's row first and spills 1.8 KB per lane
@@ -276,7 +280,7 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 #pragma unroll
       for (int k = 0; k < OMPF; ++k)
         if (p0 + k < Pairs<NS>::N)
-          iD[k] = omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[PR.i[p0 + k]][PR.j[p0 + k]]);
+          iD[k] = omega(PR.i[p0 + k], PR.j[p0 + k]);
 #pragma unroll
       for (int k = 0; k < OMPF; ++k)
         if (p0 + k < Pairs<NS>::N) asm volatile("" : "+v"(iD[k])::"memory");
@@ -300,7 +304,7 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 #pragma unroll
       for (int s = 0; s < NS; ++s)
         if (Dacc[s] * pT15 < 1e-300)
-          Ds[s] = M->Dpre[s][s] * T15 / (p * omega11<TAB>(s_om, omr0, omrs, T * M->Dieps[s][s]));
+          Ds[s] = M->Dpre[s][s] * T15 / (p * omega(s, s));
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) aux[(7 + s) * N + q] = Ds[s];

@@ -41,8 +41,8 @@ def build(out, species):
 
     def compile_(src):
         obj = os.path.join(out, os.path.basename(src) + ".o")
-        subprocess.run([CLANG, "-std=c++17", "-O1", "-fPIC", "-w", "-mfma", "-ffp-contract=fast-honor-pragmas", "-x", "c++", "-I", HERE,
-                        "-I", os.path.join(ROOT, "include"), "-I", out, "-c", src, "-o", obj], check=True)
+        subprocess.run([CLANG, "-std=c++17", "-O1", "-fPIC", "-w", "-mfma", "-ffp-contract=fast-honor-pragmas", "-x", "c++",
+                        *(["-DCPU_COUNT_CALLS"] if src.endswith(".hip") else []), "-I", HERE, "-I", os.path.join(ROOT, "include"), "-I", out, "-c", src, "-o", obj], check=True)
         return obj
     with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_, objs))
@@ -67,4 +67,5 @@ def use(lib, mp):
     L = _lib.load()
     L.cpu_capture_end.restype = C.c_void_p
     L.cpu_replay.argtypes = [C.c_void_p]
+    L.cpu_calls.restype = C.c_longlong
     return L

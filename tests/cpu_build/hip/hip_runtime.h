@@ -2,6 +2,8 @@
 // with this header in HIP's place and run the kernels here, a block's threads as
 // fibers and the blocks in turn.  Device memory is malloc's, filled with NaNs.
 #pragma once
+#include <math.h>
+
 #include <cmath>
 #include <cstddef>
 #include <cstdint>
@@ -127,3 +129,12 @@ inline hipError_t hipGraphDestroy(hipGraph_t g) { delete g; return hipSuccess; }
 inline hipError_t hipGraphExecDestroy(hipGraphExec_t g) { delete g; return hipSuccess; }
 #define HIP_SYMBOL(x) x
 inline hipError_t hipGetSymbolAddress(void** p, const void* s) { *p = const_cast<void*>(s); return hipSuccess; }
+
+// In the kernels' files: the calls of exp and log are counted.
+#ifdef CPU_COUNT_CALLS
+namespace cpu { extern long long calls; }
+inline double cpu_exp(double x) { ++cpu::calls; return exp(x); }
+inline double cpu_log(double x) { ++cpu::calls; return log(x); }
+#define exp cpu_exp
+#define log cpu_log
+#endif

@@ -11,6 +11,7 @@ dim3 threadIdx, blockIdx, blockDim, gridDim;
 namespace cpu {
 
 hipGraph_t capturing = nullptr;
+long long calls = 0;
 
 namespace {
 enum State { READY, BLOCK, WAVE, DONE };
@@ -115,6 +116,13 @@ void run(dim3 grid, dim3 block, const std::function<void()>& kernel) {
 }
 
 }  // namespace cpu
+
+// The calls of exp and log in kernels since the last time.
+extern "C" long long cpu_calls() {
+  const long long n = cpu::calls;
+  cpu::calls = 0;
+  return n;
+}
 
 // Capture as a caller's stream capture would see it.
 extern "C" void cpu_capture_begin() { hipStreamBeginCapture(nullptr, hipStreamCaptureModeGlobal); }
