@@ -632,8 +632,7 @@ static hipError_t prim_to_cons_t(const MechTables* M, const Member* mem, int nme
   return hipGetLastError();
 }
 
-// A mechanism without a table (om_tab false: a single species, or a range of
-// T* wider than the table holds) runs one block per logical block.
+// om_tab false: a single species, or a range of T* wider than the table holds.
 template <int NS>
 static hipError_t point_t(const MechTables* M, const Member* mem, int nmem, int nblocks, int grid,
                           const CallArgs& a, const double* U, double* T, double* aux, double* src, double* hrr,
@@ -646,12 +645,12 @@ static hipError_t point_t(const MechTables* M, const Member* mem, int nmem, int 
   if (cg) {   // curvilinear single grid: one block per logical block
     if (om_tab) P_(false, true, true, nblocks);
     else P_(false, true, false, nblocks);
-  } else if (!om_tab) {
-    P_(false, false, false, nblocks);
   } else if (grid < nblocks) {
-    P_(true, false, true, grid);
+    if (om_tab) P_(true, false, true, grid);
+    else P_(true, false, false, grid);
   } else {
-    P_(false, false, true, nblocks);
+    if (om_tab) P_(false, false, true, nblocks);
+    else P_(false, false, false, nblocks);
   }
 #undef P_
   return hipGetLastError();

@@ -12,6 +12,7 @@ namespace cpu {
 
 hipGraph_t capturing = nullptr;
 long long calls = 0;
+unsigned largest = 0;
 
 namespace {
 enum State { READY, BLOCK, WAVE, DONE };
@@ -85,6 +86,7 @@ void run(dim3 grid, dim3 block, const std::function<void()>& kernel) {
   blockDim = block;
   gridDim = grid;
   const unsigned nblocks = grid.x * grid.y * grid.z;
+  if (nblocks > largest) largest = nblocks;
   for (unsigned b = 0; b < nblocks; ++b) {
     blockIdx = dim3(b % grid.x, b / grid.x % grid.y, b / (grid.x * grid.y));
     any_or = 0;
@@ -121,6 +123,13 @@ void run(dim3 grid, dim3 block, const std::function<void()>& kernel) {
 extern "C" long long cpu_calls() {
   const long long n = cpu::calls;
   cpu::calls = 0;
+  return n;
+}
+
+// The largest launch's blocks since the last time.
+extern "C" unsigned cpu_largest_grid() {
+  const unsigned n = cpu::largest;
+  cpu::largest = 0;
   return n;
 }
 
