@@ -203,9 +203,16 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
       if (!conv) err = ST_NEWTON;
       else if (T < M->Tmin || T > M->Tmax) err = ST_TRANGE;
     }
-    if (err) {
-      atomicOr(status, err);
-      T = NAN;
+    if constexpr (TAB) {
+      if (err) {
+        atomicOr(status, err);
+        T = NAN;
+      }
+    } else {
+      // a branch of the whole wavefront: at nine species the compiler put a copy
+      // of the other lanes' velocity under the divergent one's execution mask
+      T = err ? NAN : T;
+      if (__any(err)) atomicOr(status, err);
     }
     Tb[G.off + q] = T;
     const double iT = 1.0 / T;

@@ -63,6 +63,8 @@ void launch(dim3 grid, dim3 block, void (*kernel)(P...), A... args) {
 inline void __syncthreads() { cpu::sync_threads(); }
 inline int __syncthreads_or(int v) { return cpu::sync_or(v); }
 inline double __shfl_xor(double v, int mask, int = 64) { return cpu::shfl_xor(v, mask); }
+// lane by lane: a lane for which p is false changes nothing in such a branch
+inline int __any(int p) { return p; }
 inline int __double2hiint(double x) {
   int64_t b;
   std::memcpy(&b, &x, 8);
