@@ -876,11 +876,13 @@ __global__ __launch_bounds__(BLK, 2) void k_adj_point(const MechTables* __restri
         Yb[k] += -Db * iDa;
         Daccb[k] = -Db * ((1.0 - Y[k]) * iDa) * iDa;
       }
-      if (pure) {
+      // a branch of the whole wavefront, its lanes' shares selected: a divergent
+      // one's execution mask is spilled here, and the compiler then stores
+      // other lanes' values under it (wild addresses at ten and twelve species)
+      if (__any(pure)) {
 #pragma unroll
         for (int k = 0; k < NS; ++k) {
-          if (!(Dacc[k] < 1e-300)) continue;
-          const double Db = pbv[(PB_D + k) * N + q];
+          const double Db = Dacc[k] < 1e-300 ? pbv[(PB_D + k) * N + q] : 0.0;
           double dd;
           const double om = omega_dT(k, k, &dd);
           const double Dk = M->Dpre[k][k] * T15 / (p * om);
