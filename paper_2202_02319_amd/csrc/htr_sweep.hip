@@ -534,7 +534,7 @@ __global__ __launch_bounds__(BLK, 3) void k_conv(const MechTables* __restrict__ 
 
 // The lean convective sweep: the tiles without TENO faces (central fluxes
 // only), at up to four blocks per CU; marks the other tiles in tcls for
-// k_conv<NS, 3>.
+// k_conv<NS, 3>.  gridDim.y: as in k_conv<NS, 0>.
 template <int NS>
 __global__ __launch_bounds__(BLK, 4) void k_conv_lean(const MechTables* __restrict__ M,
                                                       const Member* __restrict__ mem, int nmem, CallArgs A,
@@ -543,7 +543,9 @@ __global__ __launch_bounds__(BLK, 4) void k_conv_lean(const MechTables* __restri
                                                       const unsigned char* __restrict__ flagb,
                                                       double* __restrict__ partb, double psi_c,
                                                       unsigned char* __restrict__ tcls) {
-  conv_tile<NS, false, 1>(blockIdx.x, mem, nmem, A, Ub, auxb, srcb, flagb, partb, nullptr, psi_c, 0.0, tcls, 0, NS + 4);
+  const int run = (NS + 4 + gridDim.y - 1) / gridDim.y, v0 = blockIdx.y * run;
+  conv_tile<NS, false, 1>(blockIdx.x, mem, nmem, A, Ub, auxb, srcb, flagb, partb, nullptr, psi_c, 0.0, tcls, v0,
+                          min(v0 + run, NS + 4));
 }
 
 // Diffusive flux at the face between nodes qA and qB = A + e_d, in the sign
@@ -1540,22 +1542,31 @@ static hipError_t conv_t(const MechTables* M, const Member* mem, int nmem, int n
   } else if (grid < ntblocks) {
     hipLaunchKernelGGL((k_conv<NS, 1>), dim3(grid), dim3(BLK), 0, s, M, mem, nmem, ntblocks, a, U, aux, src, flag,
                        part, bits, psi_c, CT, tcls);
-  } else if (!tcls || ntblocks <= CONV_RESIDENT) {
-    // every tile in the full sweep: asked for, or all of them are on the chip at
-    // once, where the lean variant's occupancy gives nothing; of fewer tiles
-    // still, each one's variables are dealt to several blocks, whose chains of
-    // barriers then run side by side
+  } else {
+    // of few tiles, each one's variables are dealt to several blocks, whose
+    // chains of barriers then run side by side
     int runs = CONV_RESIDENT / ntblocks;
     runs = runs < 1 ? 1 : (runs > NS + 4 ? NS + 4 : runs);
-    runs = (NS + 4 + (NS + 4 + runs - 1) / runs - 1) / ((NS + 4 + runs - 1) / runs);   // no empty run
-    hipLaunchKernelGGL((k_conv<NS, 0>), dim3(ntblocks, runs), dim3(BLK), 0, s, M, mem, nmem, ntblocks, a, U, aux, src, flag,
-                       part, bits, psi_c, CT, tcls);
-  } else {
-    // central tiles in the lean variant, then the tiles with TENO faces
-    hipLaunchKernelGGL((k_conv_lean<NS>), dim3(ntblocks), dim3(BLK), 0, s, M, mem, nmem, a, U, aux, src, flag, part,
-                       psi_c, tcls);
-    hipLaunchKernelGGL((k_conv<NS, 3>), dim3(ntblocks), dim3(BLK), 0, s, M, mem, nmem, ntblocks, a, U, aux, src, flag,
-                       part, bits, psi_c, CT, tcls);
+    const int run = (NS + 4 + runs - 1) / runs;
+    runs = (NS + 4 + run - 1) / run;   // no empty run
+    const bool central = a.flags & HTR_FORCE_CENTRAL;
+    if (!tcls || (!central && runs > 1)) {
+      // every tile in the full sweep: asked for, or few enough to be dealt.  In
+      // one run each that would save a launch, and cost smooth tiles the lean
+      // variant: 43 against 29 us on 52^3 smooth cells of five species (117
+      // against 123 us where all faces are TENO's, nine species)
+      hipLaunchKernelGGL((k_conv<NS, 0>), dim3(ntblocks, runs), dim3(BLK), 0, s, M, mem, nmem, ntblocks, a, U, aux, src, flag,
+                         part, bits, psi_c, CT, tcls);
+    } else {
+      // central tiles in the lean variant, then the tiles with TENO faces if
+      // there can be any.  Where all are central, however few: 160^2 cells and
+      // nine species 13 us, 26 in the full sweep and 21 in two launches of one run
+      hipLaunchKernelGGL((k_conv_lean<NS>), dim3(ntblocks, runs), dim3(BLK), 0, s, M, mem, nmem, a, U, aux, src, flag,
+                         part, psi_c, tcls);
+      if (!central)
+        hipLaunchKernelGGL((k_conv<NS, 3>), dim3(ntblocks), dim3(BLK), 0, s, M, mem, nmem, ntblocks, a, U, aux, src, flag,
+                           part, bits, psi_c, CT, tcls);
+    }
   }
   return hipGetLastError();
 }

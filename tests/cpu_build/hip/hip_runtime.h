@@ -48,6 +48,7 @@ void sync_threads();
 int sync_or(int v);
 double shfl_xor(double v, int mask);
 void run(dim3 grid, dim3 block, const std::function<void()>& kernel);
+void note(void* kernel, unsigned blocks);
 inline void submit(std::function<void()> f) {
   if (capturing) capturing->nodes.push_back(std::move(f));
   else f();
@@ -55,6 +56,7 @@ inline void submit(std::function<void()> f) {
 template <class... P, class... A>
 void launch(dim3 grid, dim3 block, void (*kernel)(P...), A... args) {
   std::tuple<std::decay_t<P>...> t(args...);   // by value at the launch, as a graph's node keeps them
+  note((void*)kernel, grid.x * grid.y * grid.z);
   submit([=] { run(grid, block, [=] { std::apply(kernel, t); }); });
 }
 }  // namespace cpu

@@ -2,9 +2,12 @@
 // barriers (of the block, and of a wavefront of 64 for the lane exchange).
 #include <hip/hip_runtime.h>
 
+#include <dlfcn.h>
 #include <ucontext.h>
 
 #include <cstdio>
+#include <string>
+#include <utility>
 
 dim3 threadIdx, blockIdx, blockDim, gridDim;
 
@@ -12,7 +15,7 @@ namespace cpu {
 
 hipGraph_t capturing = nullptr;
 long long calls = 0;
-unsigned largest = 0;
+std::vector<std::pair<std::string, unsigned>> launches;   // names and blocks
 
 namespace {
 enum State { READY, BLOCK, WAVE, DONE };
@@ -57,6 +60,12 @@ bool open(State s, int lo, int hi) {
 }
 }  // namespace
 
+void note(void* kernel, unsigned blocks) {
+  Dl_info i{};
+  dladdr(kernel, &i);
+  launches.emplace_back(i.dli_sname ? i.dli_sname : "", blocks);
+}
+
 void sync_threads() { wait(BLOCK); }
 int sync_or(int v) {
   any_or |= v != 0;
@@ -86,7 +95,6 @@ void run(dim3 grid, dim3 block, const std::function<void()>& kernel) {
   blockDim = block;
   gridDim = grid;
   const unsigned nblocks = grid.x * grid.y * grid.z;
-  if (nblocks > largest) largest = nblocks;
   for (unsigned b = 0; b < nblocks; ++b) {
     blockIdx = dim3(b % grid.x, b / grid.x % grid.y, b / (grid.x * grid.y));
     any_or = 0;
@@ -126,12 +134,18 @@ extern "C" long long cpu_calls() {
   return n;
 }
 
-// The largest launch's blocks since the last time.
-extern "C" unsigned cpu_largest_grid() {
-  const unsigned n = cpu::largest;
-  cpu::largest = 0;
+// The blocks launched since the last time, of the largest launch (part empty) or
+// of all launches of kernels with part in their name.
+extern "C" unsigned cpu_blocks(const char* part) {
+  unsigned n = 0;
+  for (auto& l : cpu::launches)
+    if (!*part) n = l.second > n ? l.second : n;
+    else if (l.first.find(part) != std::string::npos) n += l.second;
+  cpu::launches.clear();
   return n;
 }
+
+extern "C" unsigned cpu_largest_grid() { return cpu_blocks(""); }
 
 // Capture as a caller's stream capture would see it.
 extern "C" void cpu_capture_begin() { hipStreamBeginCapture(nullptr, hipStreamCaptureModeGlobal); }
