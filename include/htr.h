@@ -414,11 +414,11 @@ htr_status htr_batch_member_max(htr_batch* b, const double* field, double* max_d
  * staging buffers hold is accepted (16x4x4, 8x8x4, 8x4x8, 4x8x8 in 3-D;
  * 16x16, 32x8, 8x32, 64x4 in 2-D; 256 in 1-D); the default is 16x4x4 in 3-D,
  * or one of the other three where the grid has fewer of its tiles, 16x16 in
- * 2-D.  The diffusive sweep works on tiles of a fixed shape (8x8x4 in 3-D,
- * 16x12 in 2-D, 192 in 1-D).  grid > 0 launches the forward
- * kernels (per-cell, sensor, both sweeps) as grid persistent blocks that
- * stride over their logical blocks; grid = 0 launches one block per
- * logical block.  Results are bitwise independent of both choices (every
+ * 2-D.  The diffusive sweep works on tiles of a shape of its own (in 3-D the
+ * one of 8x8x4, 8x4x8, 4x8x8 and 16x4x3 of which the grid has fewest, 16x12
+ * in 2-D, 192 in 1-D).  grid > 0 launches the forward kernels (per-cell,
+ * sensor, both sweeps) as grid persistent blocks that stride over their
+ * logical blocks; grid = 0 launches one block per logical block.  Results are bitwise independent of both choices (every
  * face is evaluated once with the same arithmetic).  Changing the tiling
  * synchronises the device, and it discards an ensemble's captured graph.
  * ------------------------------------------------------------------------ */

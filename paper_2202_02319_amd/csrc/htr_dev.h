@@ -274,8 +274,8 @@ hipError_t launch_bnd(int ns, const MechTables* M, const Member* mem, const Memb
                       const double* T, const double* aux, const double* src, const unsigned char* flag,
                       const double* grad, double* part, double psi_c, double CT, hipStream_t s);
 // kinds: DIFF_* of the members there are.
-constexpr unsigned DIFF_FLAT = 1u, DIFF_3D = 2u;
-inline unsigned diff_kind(const Member& M) { return M.act[0] && M.act[1] && M.act[2] ? DIFF_3D : DIFF_FLAT; }
+constexpr unsigned DIFF_FLAT = 1u, DIFF_STAGED = 2u;
+inline unsigned diff_kind(const Member& M) { return M.dtdim[0] * M.dtdim[1] * M.dtdim[2] == BLK ? DIFF_STAGED : DIFF_FLAT; }
 hipError_t launch_diff(int ns, const MechTables* M, const Member* mem, int nmem, int ntblocks, int grid, unsigned kinds,
                        const CallArgs& a,
                        const double* U, const double* Un, const double* T, const double* aux, const double* grad,

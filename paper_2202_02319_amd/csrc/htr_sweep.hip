@@ -80,14 +80,28 @@ bool tile_shape_ok(const int act[3], const int t[3], const char** why) {
   return w == nullptr;
 }
 
-// The diffusive sweep's tile for the active axes: 8 x 8 x 4 in 3-D (its 256
-// halo nodes are one per thread); for k_diff_flat 16 x 12 over the two active
-// axes of a 2-D grid (204 and 208 faces) and 192 along a 1-D grid.
+// The diffusive sweep's tile.  On 3-D grids the shape of fewest tiles among
+// k_diff's (8 x 8 x 4, 8 x 4 x 8, 4 x 8 x 8: their 256 halo nodes are one per
+// thread) and the 16 x 4 x 3 of k_diff_flat, whose tiles cost about as much
+// (0.054 against 0.055 us at 128^3 cells and nine species, up to a fifth less
+// with one, so it has the ties).  A thin grid fills no tile, so fewest tiles is
+// least time: 16384x2x2 cells 38 us a launch in 16 x 4 x 3, 80 in 8 x 8 x 4;
+// 4x256x256 53 us in 4 x 8 x 8, 84 in 8 x 8 x 4 (nine species).
+// On 2-D grids 16 x 12 over the two active axes (204 and 208 faces) and on 1-D
+// grids 192, for k_diff_flat.
 static void diff_tile_shape(const int act[3], const int n[3], int t[3]) {
   const int na = act[0] + act[1] + act[2];
   default_tile_shape(act, n, t);
   if (na == 3) {
-    t[0] = 8; t[1] = 8; t[2] = 4;
+    constexpr int shapes[4][3] = {{8, 8, 4}, {8, 4, 8}, {4, 8, 8}, {16, 4, 3}};
+    long long best = 0;
+    for (int k = 0; k < 4; ++k) {
+      long long w = 1;
+      for (int a = 0; a < 3; ++a) w *= (n[a] + shapes[k][a] - 1) / shapes[k][a];
+      if (k > 0 && (k < 3 ? w >= best : w > best)) continue;
+      best = w;
+      for (int a = 0; a < 3; ++a) t[a] = shapes[k][a];
+    }
   } else if (na == 2) {
     int k = 0;
     for (int a = 0; a < 3; ++a)
@@ -681,16 +695,16 @@ __device__ __forceinline__ void diff_dir(const MechTables* __restrict__ M, const
   __syncthreads();
 }
 
-// Members with three active axes are k_diff's, the others k_diff_flat's; each
+// Members with tiles of BLK cells are k_diff's, the others k_diff_flat's; each
 // kernel passes over the blocks of the other's.
-__device__ __forceinline__ bool three_axes(const Member& G) { return G.act[0] && G.act[1] && G.act[2]; }
+__device__ __forceinline__ bool staged(const Member& G) { return G.dtdim[0] * G.dtdim[1] * G.dtdim[2] == BLK; }
 
-// The sweep of grids with one or two active axes: diffusive flux
+// The sweep of grids with one or two active axes, and of thin ones: diffusive flux
 // differences (each face once, exchanged through LDS) added to part, then the
 // SSP-RK3 stage combination (or dU/dt when rhs_only).  Tiles of DTILE cells in
 // BLKF threads, the first DTILE own the cells, and every thread owns one face
-// per direction (a tile has at most BLKF faces along any axis), whose nodes'
-// fields it reads itself.  With one or two directions that costs fewer loads
+// per direction (a tile has at most BLKF faces along any axis: 16 x 4 x 3 has
+// 204, 240 and 256), whose nodes' fields it reads itself.  With one or two directions that costs fewer loads
 // than the staged species of k_diff cost barriers: 6.0 against 10.0 us on 256
 // cells along a line (five species), 20.0 against 23.6 us on 384x250 (nine).
 template <int NS>
@@ -768,12 +782,12 @@ __global__ __launch_bounds__(BLKF, 3) void k_diff_flat(const MechTables* __restr
                                                   const double* __restrict__ partb, double* outb, double ca,
                                                   double cb, int rhs_only) {
   if (!PERSIST) {
-    if (three_axes(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff's
+    if (staged(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff's
     diff_flat_tile<NS>(blockIdx.x, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     return;
   }
   for (int bl = blockIdx.x; bl < nlog; bl += gridDim.x) {
-    if (three_axes(mem[find_member_dtiled(mem, nmem, bl)])) continue;
+    if (staged(mem[find_member_dtiled(mem, nmem, bl)])) continue;
     diff_flat_tile<NS>(bl, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     __syncthreads();   // the next tile reuses the LDS
   }
@@ -1159,12 +1173,12 @@ __global__ __launch_bounds__(BLK, 2) void k_diff(const MechTables* __restrict__ 
                                                  const double* __restrict__ partb, double* outb, double ca,
                                                  double cb, int rhs_only) {
   if (!PERSIST) {
-    if (!three_axes(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff_flat's
+    if (!staged(mem[find_member_dtiled(mem, nmem, blockIdx.x)])) return;   // k_diff_flat's
     diff_tile<NS>(blockIdx.x, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     return;
   }
   for (int bl = blockIdx.x; bl < nlog; bl += gridDim.x) {
-    if (!three_axes(mem[find_member_dtiled(mem, nmem, bl)])) continue;
+    if (!staged(mem[find_member_dtiled(mem, nmem, bl)])) continue;
     diff_tile<NS>(bl, M, mem, nmem, A, Ub, Unb, Tb, auxb, gradb, partb, outb, ca, cb, rhs_only);
     __syncthreads();   // the next tile reuses the LDS
   }
@@ -1583,7 +1597,7 @@ static hipError_t diff_t(const MechTables* M, const Member* mem, int nmem, int n
     if (grid < ntblocks) D_(k_diff_flat, true, grid, BLKF);
     else D_(k_diff_flat, false, ntblocks, BLKF);
   }
-  if (kinds & DIFF_3D) {
+  if (kinds & DIFF_STAGED) {
     if (grid < ntblocks) D_(k_diff, true, grid, BLK);
     else D_(k_diff, false, ntblocks, BLK);
   }
