@@ -80,25 +80,31 @@ bool tile_shape_ok(const int act[3], const int t[3], const char** why) {
   return w == nullptr;
 }
 
-// The diffusive sweep's tile.  On 3-D grids the shape of fewest tiles among
+// The diffusive sweep's tile.  On 3-D grids the shape of least tiles among
 // k_diff's (8 x 8 x 4, 8 x 4 x 8, 4 x 8 x 8: their 256 halo nodes are one per
-// thread) and the 16 x 4 x 3 of k_diff_flat, whose tiles cost about as much
-// (0.054 against 0.055 us at 128^3 cells and nine species, up to a fifth less
-// with one, so it has the ties).  A thin grid fills no tile, so fewest tiles is
-// least time: 16384x2x2 cells 38 us a launch in 16 x 4 x 3, 80 in 8 x 8 x 4;
-// 4x256x256 53 us in 4 x 8 x 8, 84 in 8 x 8 x 4 (nine species).
+// thread) and the 16 x 4 x 3 of k_diff_flat: tiles of a thin grid are mostly
+// empty and cost as much.  Nine species: 16384x2x2 cells 38 us a launch in
+// 16 x 4 x 3, 80 in 8 x 8 x 4; 256x2x256 47 us in 8 x 4 x 8, 83 in 8 x 8 x 4;
+// 4x256x256 53 us in 1024 tiles of 4 x 8 x 8, 84 in 2048 of 8 x 8 x 4: with
+// rows of four a tile costs a quarter more.  16 x 4 x 3 needs a fifth less,
+// since ensembles whose members take either pay for both kernels (64 members of
+// 12 to 24 cells an axis: 7.9 against 7.3 ms a five-step run if ties are its),
+// or a tie where an axis is shorter than a tile (256x256x5 cells, one species:
+// 32 against 44 us).
 // On 2-D grids 16 x 12 over the two active axes (204 and 208 faces) and on 1-D
 // grids 192, for k_diff_flat.
 static void diff_tile_shape(const int act[3], const int n[3], int t[3]) {
   const int na = act[0] + act[1] + act[2];
   default_tile_shape(act, n, t);
   if (na == 3) {
+    const bool thin = n[0] < 8 || n[1] < 8 || n[2] < 8;
     constexpr int shapes[4][3] = {{8, 8, 4}, {8, 4, 8}, {4, 8, 8}, {16, 4, 3}};
+    const int weight[4] = {4, 4, 5, thin ? 4 : 5};
     long long best = 0;
     for (int k = 0; k < 4; ++k) {
-      long long w = 1;
+      long long w = weight[k];
       for (int a = 0; a < 3; ++a) w *= (n[a] + shapes[k][a] - 1) / shapes[k][a];
-      if (k > 0 && (k < 3 ? w >= best : w > best)) continue;
+      if (k > 0 && (k == 3 && thin ? w > best : w >= best)) continue;
       best = w;
       for (int a = 0; a < 3; ++a) t[a] = shapes[k][a];
     }

@@ -45,6 +45,20 @@ def test_blocks_cpu(built, monkeypatch, n):
     assert normwise(d.numpy(), o.rhs(U.numpy(), case.T.copy(), t=2e-8)).max() <= 1e-12
 
 
+@pytest.mark.parametrize("n,blocks", [((9, 17, 5), 10),     # 12, 10, 9 and 10 tiles: 4x8x8 not for a tenth
+                                      ((4, 17, 17), 9),     # 15, 15, 9 and 30: but for more than a fifth
+                                      ((10, 17, 9), 18)])   # 18, 20, 18 and 15: 16x4x3 not for less than a fifth
+def test_weights_cpu(built, monkeypatch, n, blocks):
+    lib = cpu_build.use(built, monkeypatch)
+    case = _case(n)
+    g = htr.Context.from_case(case)
+    U = torch.tensor(Oracle(case).prim_to_cons())
+    lib.cpu_blocks(b"")
+    htr.htr_rhs(g, U, torch.tensor(case.T), 2e-8, case.laser, torch.empty_like(U))
+    htr.htr_check(g)
+    assert lib.cpu_blocks(b"k_diff") == blocks
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n", SHAPES)
 def test_rhs(n):
