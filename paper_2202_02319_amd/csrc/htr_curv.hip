@@ -310,11 +310,59 @@ __global__ __launch_bounds__(BLK) void k_curv_conv(const Member* __restrict__ me
   }
 }
 
-// Tile of the diffusive kernel: BLK cells over the active axes.
-__host__ __device__ inline void curv_tile(const int act[3], int T[3]) {
+constexpr int CBOX = 10 * 10 * 6;   // a tile with its layer: 3-D the largest (2-D 18 x 18, 1-D 258)
+
+// Tile of the diffusive kernel: BLK cells over the active axes.  On a 3-D grid
+// the shape of least tiles, those with rows of four counted a quarter more
+// (83x61x37 cells, nine species: 101 us a launch in 840 tiles of 4 x 8 x 8, 82
+// in 880 of 8 x 8 x 4; 2x256x256 70 us in 1024 and 124 in 2048).  A grid of at
+// most four cells along every axis but one fills few of a tile's threads, and
+// takes the longest tile that the block can stage (BLK nodes beside its faces,
+// 64 faces of a last layer, CBOX nodes): 16384x2x2 cells 58 us in 31 x 2 x 2,
+// 117 in 8 x 8 x 4; 16384x2 25 us in 64 x 2, 51 in 16 x 16.
+static void curv_tile(const int act[3], const int n[3], int T[3]) {
   const int na = (act[0] != 0) + (act[1] != 0) + (act[2] != 0);
-  for (int a = 0; a < 3; ++a) T[a] = na == 3 ? (a < 2 ? 8 : 4) : (act[a] ? (na == 2 ? 16 : BLK) : 1);
+  for (int a = 0; a < 3; ++a) T[a] = act[a] ? (na == 2 ? 16 : BLK) : 1;
   if (na == 0) T[0] = BLK;
+  if (na < 2) return;
+  auto tiles = [&](const int t[3]) {
+    long long w = 1;
+    for (int a = 0; a < 3; ++a) w *= (n[a] + t[a] - 1) / t[a];
+    return w;
+  };
+  constexpr int shapes[3][3] = {{8, 8, 4}, {8, 4, 8}, {4, 8, 8}}, weight[3] = {4, 4, 5};
+  long long best = 4 * tiles(T);
+  for (int k = 0; k < 3 && na == 3; ++k) {
+    const long long w = weight[k] * tiles(shapes[k]);
+    if (k > 0 && w >= best) continue;
+    best = w;
+    for (int a = 0; a < 3; ++a) T[a] = shapes[k][a];
+  }
+  for (int d = 0; d < 3; ++d) {
+    int t[3];
+    bool thin = act[d];
+    for (int a = 0; a < 3; ++a) {
+      thin = thin && (a == d || n[a] <= 4);
+      t[a] = act[a] ? n[a] : 1;
+    }
+    if (!thin) continue;
+    auto fits = [&] {
+      const int cells = t[0] * t[1] * t[2];
+      int beside = 0, box = 1, most = 0;
+      for (int a = 0; a < 3; ++a)
+        if (act[a]) {
+          beside += 2 * (cells / t[a]);
+          box *= t[a] + 2;
+          most = cells / t[a] > most ? cells / t[a] : most;
+        }
+      return cells <= BLK && beside <= BLK && box <= CBOX && most <= 64;
+    };
+    for (t[d] = 64; t[d] > 1 && !fits();) --t[d];
+    if (4 * tiles(t) < best) {
+      best = 4 * tiles(t);
+      for (int a = 0; a < 3; ++a) T[a] = t[a];
+    }
+  }
 }
 
 // Mapped diffusive fluxes, their and the convective ones' differences, and the
@@ -339,10 +387,10 @@ __host__ __device__ inline void curv_tile(const int act[3], int T[3]) {
 // Mole fractions, index-space differences, face fluxes and update as four
 // launches through memory (about 330 values a cell written and read back) took
 // 65 + 258 + 1450 + 446 us.
-constexpr int CBOX = 10 * 10 * 6;   // a tile with its layer: 3-D the largest (2-D 18 x 18, 1-D 258)
 template <int NS>
 __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restrict__ M, const Member* __restrict__ mem,
-                                                      CurvGeom g, CallArgs A, const double* __restrict__ U,
+                                                      CurvGeom g, CallArgs A, int3 tile,
+                                                      const double* __restrict__ U,
                                                       const double* Un, const double* __restrict__ Tf,
                                                       const double* __restrict__ aux, const double* __restrict__ src,
                                                       const double* __restrict__ ffc, double* out, double ca,
@@ -353,14 +401,15 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
   const int t = threadIdx.x;
   const long long N = G.N;
   const bool act[3] = {G.act[0] != 0, G.act[1] != 0, G.act[2] != 0};
-  int T[3], nt[3], o[3];
-  curv_tile(G.act, T);
+  const int T[3] = {tile.x, tile.y, tile.z}, cells = T[0] * T[1] * T[2];
+  int nt[3], o[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) nt[a] = (G.n[a] + T[a] - 1) / T[a];
   tile_origin_of(T, nt, gridDim.x, blockIdx.x, o);
-  const int l[3] = {t % T[0], (t / T[0]) % T[1], t / (T[0] * T[1])};
+  const int tc = t < cells ? t : 0;   // threads past a long tile's cells repeat its first
+  const int l[3] = {tc % T[0], (tc / T[0]) % T[1], tc / (T[0] * T[1])};
   const int gc[3] = {o[0] + l[0], o[1] + l[1], o[2] + l[2]};
-  const bool valid = gc[0] < G.n[0] && gc[1] < G.n[1] && gc[2] < G.n[2];
+  const bool valid = t < cells && gc[0] < G.n[0] && gc[1] < G.n[1] && gc[2] < G.n[2];
   // grid index of the node at h in the tile (-1 .. T along an active axis)
   auto node = [&](int h0, int h1, int h2) {
     return lin(G, wrapi(o[0] + h0, G.n[0]), wrapi(o[1] + h1, G.n[1]), wrapi(o[2] + h2, G.n[2]));
@@ -413,7 +462,7 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
     int k = t;   // the layers below and above along each axis
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      const int S = BLK / T[d], cnt = p[d] ? 2 * S : 0;
+      const int S = cells / T[d], cnt = p[d] ? 2 * S : 0;
       if (k >= 0 && k < cnt) {
         const int x = k % S, w = k < S ? -1 : T[d], Te = d == 0 ? T[1] : T[0];
         const int x0 = x % Te, x1 = x / Te;
@@ -443,7 +492,7 @@ __global__ __launch_bounds__(BLK, 2) void k_curv_diff(const MechTables* __restri
   // the extra face's direction (one per wavefront), its slots and strides
   const int xd = __builtin_amdgcn_readfirstlane(t >> 6) - 1, lane = t & 63;
   const bool has_x = xd >= 0 && (xd == 0 ? act[0] : (xd == 1 ? act[1] : act[2])) &&
-                     lane < BLK / (xd == 0 ? T[0] : (xd == 1 ? T[1] : T[2]));
+                     lane < cells / (xd == 0 ? T[0] : (xd == 1 ? T[1] : T[2]));
   int sx = 0, xn = 0, x1 = 0, x2 = 0;
   qf[3] = qc;
   if (has_x) {
@@ -743,9 +792,9 @@ static hipError_t diff_t(const MechTables* M, const Member& host, const Member* 
                          const double* src, const double* ffc, double* out, double ca, double cb, int rhs_only,
                          hipStream_t s) {
   int td[3], nb = 1;
-  curv_tile(host.act, td);
+  curv_tile(host.act, host.n, td);
   for (int k = 0; k < 3; ++k) nb *= (host.n[k] + td[k] - 1) / td[k];
-  hipLaunchKernelGGL(k_curv_diff<NS>, dim3(nb), dim3(BLK), 0, s, M, mem, g, a, U, Un, T, aux, src, ffc, out, ca, cb,
+  hipLaunchKernelGGL(k_curv_diff<NS>, dim3(nb), dim3(BLK), 0, s, M, mem, g, a, int3{td[0], td[1], td[2]}, U, Un, T, aux, src, ffc, out, ca, cb,
                      rhs_only);
   return hipGetLastError();
 }
