@@ -159,8 +159,9 @@ typedef struct {
  * works on it (htr_rhs, htr_cells, htr_stable_dt, htr_rk3_step); the tape,
  * the adjoint and the tiling/autotune calls return HTR_EUNSUPPORTED.
  * The host arrays are copied; the context owns, besides the rectilinear
- * context's scratch, 22 N doubles of geometry (metric terms, face metric
- * terms, coordinates) and (10 ns + 36) N doubles of per-stage scratch.
+ * context's scratch, 49 N doubles of geometry (metric terms, face metric
+ * terms, the derivatives at the faces that the diffusive fluxes take, and
+ * coordinates) and 3 (ns + 4) N doubles of per-stage scratch.
  * Creation blocks: it runs the metric kernels and checks J on the host.
  * On such a grid the laser centre is a physical position, the Gaussian is
  * summed over the lattice images, and cell volumes (J objective) are 1/J.
@@ -418,9 +419,10 @@ htr_status htr_batch_member_max(htr_batch* b, const double* field, double* max_d
  * one of 8x8x4, 8x4x8, 4x8x8 and 16x4x3 of which the grid has fewest, 16x12
  * in 2-D, 192 in 1-D).  grid > 0 launches the forward kernels (per-cell,
  * sensor, both sweeps) as grid persistent blocks that stride over their
- * logical blocks; grid = 0 launches one block per logical block.  Results are bitwise independent of both choices (every
- * face is evaluated once with the same arithmetic).  Changing the tiling
- * synchronises the device, and it discards an ensemble's captured graph.
+ * logical blocks; grid = 0 launches one block per logical block.  Results
+ * are bitwise independent of both choices (every face is evaluated once with
+ * the same arithmetic).  Changing the tiling synchronises the device, and it
+ * discards an ensemble's captured graph.
  * ------------------------------------------------------------------------ */
 /* HTR_OK if shape[3] is a valid tile for a grid of n[3] cells, else
  * HTR_EINVAL with the reason in htr_last_error.  Host only. */
@@ -449,7 +451,9 @@ htr_status htr_batch_autotune(htr_batch* b, const double* U, double* T_io, doubl
  * launches: a lean variant, with fewer registers and more waves per SIMD,
  * does the tiles none of whose faces takes the TENO path and marks the
  * others, which the full sweep then does; split = 0 runs every tile in the
- * full sweep.  Results are bitwise the same; htr_autotune and
+ * full sweep.  At split = 1 too there is one launch where one is enough: of
+ * the lean variant with HTR_FORCE_CENTRAL, else of the full sweep on at most
+ * 384 tiles, each one's variables dealt to several blocks.  Results are bitwise the same; htr_autotune and
  * htr_batch_autotune time both.  HTR_EINVAL for split outside {0, 1};
  * curvilinear contexts: HTR_EUNSUPPORTED.  Changing it discards an
  * ensemble's captured graph. */

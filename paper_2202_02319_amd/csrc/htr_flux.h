@@ -73,7 +73,9 @@ __device__ __forceinline__ unsigned teno6_pattern(double b0, double b1, double b
 // of the undivided differences of h (exact rewritings of their sums), 16 times
 // their values for f: differences of nearby values are exact, so nearly
 // uniform data keep their digits, and with the differences shared the pattern
-// takes 55 operations up to tau where the expanded sums take 95.
+// takes 55 operations up to tau where the expanded sums take 95.  Cut-offs
+// within rounding of CT can fall either way under another arrangement of the
+// same sums (as in any arithmetic that isn't the oracle's bit for bit).
 __device__ __forceinline__ unsigned teno6_decide(const double h[6], double CT) {
   const double e0 = h[1] - h[0], e1 = h[2] - h[1], e2 = h[3] - h[2], e3 = h[4] - h[3], e4 = h[5] - h[4];
   const double c0 = e1 - e0, c1 = e2 - e1, c2 = e3 - e2, c3 = e4 - e3;
@@ -177,11 +179,6 @@ __device__ __forceinline__ double node_flux(int v, int d, double U, double ud, d
 __device__ __forceinline__ double hRTi(const MechTables* __restrict__ M, int s, double T, double iT) {
   const double* a = M->hc[s];
   return a[0] + T * (a[1] + T * (a[2] + T * (a[3] + T * a[4]))) + a[5] * iT;
-}
-
-__device__ __forceinline__ double hRTs(const MechTables* __restrict__ M, int s, double T) {
-  const double* a = M->hc[s];
-  return a[0] + T * (a[1] + T * (a[2] + T * (a[3] + T * a[4]))) + a[5] / T;
 }
 
 }  // namespace htr

@@ -459,8 +459,8 @@ __device__ __forceinline__ void point_block(int bl, const MechTables* __restrict
 // the mixture's polynomials in the Newton iteration, Wilke's pairs taken
 // once and the short exponentials brought it from 644 to 397 us at 128^3 cells,
 // nine species and twenty reactions (1257 to 740 us on the 256x128x128 mixing
-// layer); its bytes, read and written once, take 153 us at the 4.7 TB/s of a
-// large copy.
+// layer); its 41 doubles a cell, read or written once (688 MB), take 146 us at
+// the 4.7 TB/s of a large copy.
 template <int NS, bool PERSIST, bool CURV, bool TAB>
 __global__ __launch_bounds__(BLK, NS <= 9 ? 3 : 2) void k_point(const MechTables* __restrict__ M,
                                                                 const Member* __restrict__ mem, int nmem, int nlog,

@@ -8,11 +8,13 @@
 // second-order central differences for the diffusive fluxes; Methods › Solver eqs.
 // (1)-(3), (5), (6) for the flux vectors.
 //
-// Two tiled kernels per stage: k_conv (sources and convective flux
+// Two tiled sweeps per stage: k_conv (sources and convective flux
 // differences, one block per 256-cell tile with the tile and its halo staged
-// in LDS) and k_diff (diffusive flux differences and the stage update, one
-// block per 256-cell tile of its own).  Every face is evaluated once, so the
-// scheme is exactly conservative.
+// in LDS), with k_conv_lean for the tiles without TENO faces; and k_diff
+// (diffusive flux differences and the stage update, one block per 256-cell
+// tile of its own, on 3-D grids) or k_diff_flat (tiles of 192 cells, on grids
+// of fewer axes and thin ones).  Every face is evaluated once, so the scheme is
+// exactly conservative.  k_bnd does the cells next to bounded boundaries.
 
 #include <math.h>
 
@@ -801,7 +803,9 @@ __global__ __launch_bounds__(BLKF, 3) void k_diff_flat(const MechTables* __restr
 
 // Diffusive flux differences added to part, then the SSP-RK3 stage
 // combination (or dU/dt when rhs_only), on the diffusive sweep's own tiles
-// (dtdim, BLK cells, one per thread).
+// (dtdim, BLK cells, one per thread; three active axes: only their tiles have
+// BLK cells.  The tests of act all hold, and stay: without them the compiler
+// moves every row's loads up and spills 1 KB a thread, 1305 us at 128^3).
 //
 // Thread t owns cell t, its box node and one halo node, and the lower face of
 // its cell along every axis; the upper faces of the tile's last layer along
